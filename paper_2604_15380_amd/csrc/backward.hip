@@ -321,7 +321,36 @@ struct HeadBwdArgs {
   void* gs;                      // out: dE/ds [N][F]
   void* gh;                      // blended heads: out dE_h/ds [N][H][F] instead
   int H;
+  // wide branches: only the shared layers run here (nb = 0), from dE/dY; with
+  // blended heads the sum over an atom's kept heads of w dE_h/dY is formed
+  // first (the shared layers are the same for every head)
+  const void* dy;                // [N][ky], blended [N][H][ky]
+  int ky;
+  const void* hw;                // blended: head weights [B][H], else null
+  double skip;
+  const int32_t* atom_struct;
 };
+
+// dE/dY of atom i, column c.
+template <class A>
+__device__ __forceinline__ A dy_at(const HeadBwdArgs& a, size_t i, int c) {
+  const A* dy = (const A*)a.dy;
+  if (!a.hw) return dy[i * a.ky + c];
+  const A* w = (const A*)a.hw + (size_t)a.atom_struct[i] * a.H;
+  const A skip = (A)a.skip;
+  A y = 0;
+  for (int h = 0; h < a.H; ++h)
+    if (w[h] >= skip) y += w[h] * dy[(i * a.H + h) * a.ky + c];
+  return y;
+}
+
+// no shared layers: dE/ds = dE/dY (ky = F)
+template <class A>
+__global__ void __launch_bounds__(256) k_dy_sum(HeadBwdArgs a) {
+  const size_t tot = (size_t)a.N * a.ky;
+  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < tot; x += (size_t)gridDim.x * blockDim.x)
+    ((A*)a.gs)[x] = dy_at<A>(a, x / a.ky, (int)(x % a.ky));
+}
 
 template <class Q>
 __device__ __forceinline__ typename Q::A packed_w0(const DenseDev& L, int k) {
@@ -358,8 +387,10 @@ __device__ void heads_bwd_tile(const HeadBwdArgs& a, int head, const int* idx, t
   // the output row of atom g: dE/ds, or dE_h/ds of this head when blended
   A* gs = (A*)a.gs;
   auto out_row = [&](int g) { return a.gh ? (A*)a.gh + ((size_t)g * a.H + head) * F : gs + (size_t)g * F; };
-  const DenseDev Lout = layer(nl - 1, false);
-  if (nl == 1) {
+  // hidden layers: all but the output one, or (dE/dY given) every layer
+  const int nhid = a.dy ? nl : nl - 1;
+  const DenseDev Lout = a.dy ? DenseDev{} : layer(nl - 1, false);
+  if (nl == 1 && !a.dy) {
     for (int x = threadIdx.x; x < TM * F; x += blockDim.x) {
       const int r = x / F, c = x % F;
       if (idx[r] >= 0) out_row(idx[r])[c] = c < Lout.din ? packed_w0<P>(Lout, c) : A(0);
@@ -375,7 +406,7 @@ __device__ void heads_bwd_tile(const HeadBwdArgs& a, int head, const int* idx, t
   __syncthreads();
   int cur = 0;
   // forward through every layer but the output one, keeping z
-  for (int m = 0; m + 1 < nl; ++m) {
+  for (int m = 0; m < nhid; ++m) {
     const DenseDev L = layer(m, false);
     T* dst = Y[cur ^ 1];
     dense_tiles<P, 1, NW>(Y[cur], a.ldw, L, [&](int ct, C* acc) {
@@ -391,8 +422,17 @@ __device__ void heads_bwd_tile(const HeadBwdArgs& a, int head, const int* idx, t
     __syncthreads();
     cur ^= 1;
   }
-  // delta of the last hidden layer: w_out * silu'(z)
-  {
+  // delta of the last hidden layer: w_out * silu'(z), or dE/dY * silu'(z)
+  if (a.dy) {
+    const int m = nhid - 1;
+    for (int x = threadIdx.x; x < TM * a.ky; x += blockDim.x) {
+      const int r = x / a.ky, c = x % a.ky;
+      A dl = 0;
+      if (idx[r] >= 0)
+        dl = dy_at<A>(a, idx[r], c) * dsilu<A>(scr[((size_t)blockIdx.x * TM + r) * a.sw + a.zoff[m] + c]);
+      Y[cur][r * a.ldw + c] = P::st(dl);
+    }
+  } else {
     const int m = nl - 2;
     const int w = pad32(Lout.din);
     for (int x = threadIdx.x; x < TM * w; x += blockDim.x) {
@@ -403,7 +443,7 @@ __device__ void heads_bwd_tile(const HeadBwdArgs& a, int head, const int* idx, t
     }
   }
   __syncthreads();
-  for (int m = nl - 2; m >= 0; --m) {
+  for (int m = nhid - 1; m >= 0; --m) {
     const DenseDev LT = layer(m, true);
     T* dst = Y[cur ^ 1];
     dense_tiles<P, 1, NW>(Y[cur], a.ldw, LT, [&](int ct, C* acc) {
@@ -1698,7 +1738,7 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
   // no head tile: its dE/ds stays NaN, so are its structure's forces (as the
   // forward's energy of that structure).  No edge leaves a structure and
   // every dense product keeps atoms in their own rows, so it stays there.
-  if (ba.dataset_id && !ba.blend)
+  if (ba.dataset_id && !ba.blend && !pm->branch_table)
     k_fill<A><<<grid_of((size_t)N * F, 256), 256, 0, st>>>((size_t)N * F, (A*)ba.gs,
                                                            (A)__builtin_nan(""));
   // heads
@@ -1708,8 +1748,15 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
     ha.N = N;
     ha.F = F;
     ha.ns = (int)pm->shared.size();
-    ha.nb = (int)hp.branch_dims.size();
+    // wide branches went through the reverse products in the forward's chunks
+    const bool wide_branch = pm->branch_table != nullptr;
+    ha.nb = wide_branch ? 0 : (int)hp.branch_dims.size();
     if (ha.ns > 16 || ha.nb > 16 || ha.ns + ha.nb > 32) return hipErrorInvalidValue;
+    ha.dy = wide_branch ? ba.g_heads : nullptr;
+    ha.ky = branch_ky(hp);
+    ha.hw = ba.blend ? ba.hw : nullptr;
+    ha.skip = ba.skip;
+    ha.atom_struct = g->atom_struct;
     int wmax = F, off = 0;
     for (int m = 0; m < ha.ns; ++m) {
       ha.shared[m] = pm->shared[m];
@@ -1720,7 +1767,7 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
       ha.bdout[m] = hp.branch_dims[m];
       if (m + 1 < ha.nb) wmax = wmax > pad32(hp.branch_dims[m]) ? wmax : pad32(hp.branch_dims[m]);
     }
-    for (int m = 0; m + 1 < ha.ns + ha.nb; ++m) {
+    for (int m = 0; m + (wide_branch ? 0 : 1) < ha.ns + ha.nb; ++m) {
       ha.zoff[m] = off;
       off += m < ha.ns ? pad32(hp.shared_dims[m]) : pad32(hp.branch_dims[m - ha.ns]);
     }
@@ -1733,7 +1780,7 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
     ha.sw = ba.scratch_w;
     ha.gs = ba.gs;
     ha.xbuf = ba.xbuf;
-    ha.gh = ba.blend ? ba.g_heads : nullptr;
+    ha.gh = ba.blend && !wide_branch ? ba.g_heads : nullptr;
     ha.H = hp.n_heads;
     const bool hgx = (size_t)2 * 16 * ha.ldw * sizeof(T) > 150 * 1024;
     const size_t smem = hgx ? 0 : (size_t)2 * 16 * ha.ldw * sizeof(T);
@@ -1743,7 +1790,7 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
                     : allow_lds(k_heads_bwd<P, F, false, HB_NW_NARROW>, smem));
     if (e != hipSuccess) return e;
     int grid;
-    if (ba.dataset_id || ba.blend) {
+    if ((ba.dataset_id || ba.blend) && !wide_branch) {
       // the forward's grouping: tiles of atoms of one head (blended: of
       // every kept (atom, head) entry)
       ha.order = ba.head_order;
@@ -1759,10 +1806,11 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
       grid = grid < HB_GRID ? grid : HB_GRID;
     }
     if (hgx && (size_t)grid * 2 * 16 * ha.ldw * sizeof(T) > ba.xbuf_bytes) return hipErrorInvalidValue;
-    if (hgx) k_heads_bwd<P, F, true, HB_NW_WIDE><<<grid, 64 * HB_NW_WIDE, 0, st>>>(ha);
+    if (wide_branch && ha.ns == 0) k_dy_sum<A><<<grid_of((size_t)N * F, 256), 256, 0, st>>>(ha);
+    else if (hgx) k_heads_bwd<P, F, true, HB_NW_WIDE><<<grid, 64 * HB_NW_WIDE, 0, st>>>(ha);
     else if (wide) k_heads_bwd<P, F, false, HB_NW_WIDE><<<grid, 64 * HB_NW_WIDE, smem, st>>>(ha);
     else k_heads_bwd<P, F, false, HB_NW_NARROW><<<grid, 64 * HB_NW_NARROW, smem, st>>>(ha);
-    if (ba.blend)
+    if (ba.blend && !wide_branch)
       k_blend_grad<A><<<grid_of((size_t)N * F, 256), 256, 0, st>>>(N, hp.n_heads, F, (A)ba.skip, g->atom_struct,
                                                                     (const A*)ba.hw, (const A*)ba.g_heads,
                                                                     (A*)ba.gs);

@@ -10,6 +10,7 @@
 //   e [N] (accumulation type).  Edges: CSR sorted by receiver.
 #include <type_traits>
 
+#include "branchgemm.h"
 #include "mfma.h"
 
 namespace {
@@ -1079,16 +1080,17 @@ __global__ void __launch_bounds__(64) k_head_plan(int n_heads, int TM, HeadPlan*
     p->n_tiles = t;
   }
   __syncthreads();
-  if (h < n_heads) {
-    const int c = p->count[h], s0 = start[h];
-    p->start[h] = s0;
-    for (int k = 0; k * TM < c; ++k) {
+  if (h < n_heads) p->start[h] = start[h];
+  // the heads in turn, each one's tiles by all lanes
+  for (int q = 0; q < n_heads; ++q) {
+    const int c = p->count[q], s0 = start[q];
+    for (int k = threadIdx.x; k * TM < c; k += 64) {
       HeadTile tl;
-      tl.head = h;
+      tl.head = q;
       tl.begin = s0 + k * TM;
       tl.end = min(s0 + (k + 1) * TM, s0 + c);
       tl.pad = 0;
-      tiles[tbase[h] + k] = tl;
+      tiles[tbase[q] + k] = tl;
     }
   }
 }
@@ -1138,6 +1140,10 @@ struct HeadArgs {
   void* e;       // [N]: one dataset's head per atom
   void* eh;      // [N][H]: blended heads (e unused), or null
   int H;
+  // wide branches: write the shared layers' output Y [N][planes][ky] (the
+  // operand rows of branch.hip) and stop there
+  void* y_out;
+  int ky;
 };
 
 // Element k of output row 0 of a packed dense layer (the B fragment order).
@@ -1203,6 +1209,21 @@ __global__ void __launch_bounds__(64 * NW) k_heads(HeadArgs a) {
     __syncthreads();
     S = dst;
     ld_S = ld;
+  }
+  if (a.y_out) {
+    for (int x = threadIdx.x; x < TM * a.ky; x += blockDim.x) {
+      const int r = x / a.ky, c = x % a.ky;
+      if (idx[r] < 0) continue;
+      const T y = S[r * ld_S + c];
+      if constexpr (P::PREC == PAINN_FP32) {
+        uint32_t p[3];
+        split3(y, p);
+        for (int k = 0; k < 3; ++k) ((bf16_t*)a.y_out)[((size_t)idx[r] * 3 + k) * a.ky + c] = (bf16_t)(p[k] >> 16);
+      } else {
+        ((T*)a.y_out)[(size_t)idx[r] * a.ky + c] = y;
+      }
+    }
+    return;
   }
   auto branch = [&](int m) {
     DenseDev L;
@@ -1782,6 +1803,12 @@ __global__ void __launch_bounds__(256) k_blend_reduce(int N, int H, A skip, cons
   e[i] = y;
 }
 
+template <class A>
+__global__ void __launch_bounds__(256) k_nan_rows(size_t n, A* __restrict__ p) {
+  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < n; x += (size_t)gridDim.x * blockDim.x)
+    p[x] = (A)NAN;
+}
+
 // Dynamic LDS beyond 64 KiB must be allowed once per kernel.
 template <class P, int F, int RT, int NW>
 hipError_t heads_allow_lds(size_t smem) {
@@ -1819,8 +1846,12 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
   HeadArgs ha;
   ha.N = N;
   ha.ns = (int)pm->shared.size();
-  ha.nb = (int)hp.branch_dims.size();
-  if (hp.n_heads > HEADS_MAX || ha.ns > 16 || ha.nb > 16) return hipErrorInvalidValue;
+  // wide branches: this kernel runs the shared layers only
+  const bool wide_branch = pm->branch_table != nullptr;
+  ha.nb = wide_branch ? 0 : (int)hp.branch_dims.size();
+  ha.y_out = nullptr;
+  ha.ky = 0;
+  if (hp.n_heads > HEADS_MAX || ha.ns > 16 || hp.branch_dims.size() > 16) return hipErrorInvalidValue;
   int ws = 0, wb = 0;   // widest shared / stored branch layer (padded)
   for (int m = 0; m < ha.ns; ++m) {
     ha.shared[m] = pm->shared[m];
@@ -1903,9 +1934,10 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
     const A* hw = fa.blend ? (const A*)fa.hw : nullptr;
     const A skip = (A)fa.skip;
     const int nb256 = (N + 255) / 256;
+    const int TMP = !wide_branch ? TM : N < BRANCH_SMALL_ATOMS ? BRANCH_TM_SMALL : BRANCH_TM;
     k_head_clear<<<1, 64, 0, st>>>(plan);
     k_head_count<A><<<nb256, 256, 0, st>>>(N, H, fa.dataset_id, hw, skip, fa.g->atom_struct, plan, (A*)fa.e);
-    k_head_plan<<<1, 64, 0, st>>>(H, TM, plan, tiles);
+    k_head_plan<<<1, 64, 0, st>>>(H, TMP, plan, tiles);
     k_head_scatter<A><<<nb256, 256, 0, st>>>(N, H, fa.dataset_id, hw, skip, fa.g->atom_struct, plan,
                                              fa.head_order);
     ha.order = fa.head_order;
@@ -1921,12 +1953,54 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
     ha.tiles = nullptr;
     ha.plan = nullptr;
   }
-  hipError_t e;
-  int hmax = 0;   // widest hidden head layer
+  hipError_t e = hipSuccess;
+  int hmax = 0;   // widest hidden head layer of this kernel
   for (int d : hp.shared_dims) hmax = hmax > d ? hmax : d;
-  for (size_t m = 0; m + 1 < hp.branch_dims.size(); ++m) hmax = hmax > hp.branch_dims[m] ? hmax : hp.branch_dims[m];
+  for (int m = 0; m + 1 < ha.nb; ++m) hmax = hmax > hp.branch_dims[m] ? hmax : hp.branch_dims[m];
   const bool wide = hmax >= HEADS_WIDE;
-  if (RT == 4) e = launch_heads_rt<P, F, 4>(st, ha, grid, smem, wide);
+  if (wide_branch) {
+    BranchArgs b{};
+    b.ky = branch_ky(hp);
+    const size_t ybytes = ((size_t)N * branch_row_bytes(P::PREC, b.ky) + 255) & ~(size_t)255;
+    if (ybytes > fa.branch_scratch_bytes) return hipErrorInvalidValue;
+    void* y = fa.branch_scratch;
+    if (ha.ns > 0) {
+      HeadArgs hs = ha;
+      hs.order = nullptr;
+      hs.tiles = nullptr;
+      hs.plan = nullptr;
+      hs.y_out = y;
+      hs.ky = b.ky;
+      const int gs = (N + TM - 1) / TM;
+      if (RT == 4) e = launch_heads_rt<P, F, 4>(st, hs, gs, smem, wide);
+      else if (RT == 2) e = launch_heads_rt<P, F, 2>(st, hs, gs, smem, wide);
+      else e = launch_heads_rt<P, F, 1>(st, hs, gs, smem, wide);
+    } else {
+      e = launch_branch_rows(st, P::PREC, N, F, fa.s, y);
+    }
+    if (e != hipSuccess) return e;
+    b.pm = pm;
+    b.branch_dims = &hp.branch_dims;
+    b.N = N;
+    b.H = H;
+    b.small = N < BRANCH_SMALL_ATOMS;
+    b.tiles = ha.tiles;
+    b.plan = ha.plan;
+    b.order = ha.order;
+    const int TMP = b.small ? BRANCH_TM_SMALL : BRANCH_TM;
+    b.max_tiles = ha.tiles ? (long long)N * (fa.blend ? H : 1) / TMP + H : (N + TMP - 1) / TMP;
+    b.y = y;
+    b.e = fa.e;
+    b.eh = ha.eh;
+    b.dy = fa.dy;
+    b.scratch = (char*)y + ybytes;
+    b.scratch_bytes = fa.branch_scratch_bytes - ybytes;
+    // an atom of a structure with an invalid dataset id is in no tile: its
+    // dE/dY is NaN, so are its forces
+    if (fa.dy && fa.dataset_id && !fa.blend)
+      k_nan_rows<A><<<grid_for((size_t)N * b.ky, 256), 256, 0, st>>>((size_t)N * b.ky, (A*)fa.dy);
+    e = launch_branch(st, P::PREC, b);
+  } else if (RT == 4) e = launch_heads_rt<P, F, 4>(st, ha, grid, smem, wide);
   else if (RT == 2) e = launch_heads_rt<P, F, 2>(st, ha, grid, smem, wide);
   else e = launch_heads_rt<P, F, 1>(st, ha, grid, smem, wide);
   if (e == hipSuccess && fa.blend)

@@ -140,6 +140,13 @@ struct PrecModel {      // the model cast and packed for one precision
   std::vector<DenseDev> shared;                 // shared head layers
   std::vector<std::vector<DenseDev>> branch;    // [head][layer]
   void* head_table = nullptr;                   // device [head][layer][2] = (w, b)
+  // wide branches (a hidden branch layer at least BRANCH_WIDE wide) are packed
+  // for the matrix products of branch.hip instead: device table of pointers
+  // [head][branch layer][4] = (w, bias, w^T, plain weights of the 1-wide
+  // output layer); branch_stride = 4 branch layers.  Null: narrow branches.
+  void* branch_table = nullptr;
+  int branch_stride = 0;
+  std::vector<void*> branch_ptrs;               // the table's host copy
   std::vector<DenseDev> blend;                  // branch-weighting MLP (empty: none)
   // reverse pass: transposed shared and branch layers (the branch's output
   // layer has none), device table [head][layer][2] = (w^T, null)
@@ -171,6 +178,7 @@ struct painn_ctx {
   // forward workspace (grown on demand)
   void* ws = nullptr;
   size_t ws_bytes = 0;
+  bool ws_tight = false;   // a workspace with the full branch scratch did not fit
   // reverse-pass workspace (saved activations and gradients; grown on demand)
   void* bws = nullptr;
   size_t bws_bytes = 0;
@@ -264,6 +272,12 @@ struct ForwardArgs {
   void* comp;
   void* hw;
   void* eh;
+  // wide branches: scratch for Y and the branch layers' activations (it shares
+  // the space of v, h and the basis rows, which the heads do not read), and,
+  // with forces, dE/dY per atom or (atom, head) [.][ky] (accumulation type)
+  void* branch_scratch;
+  size_t branch_scratch_bytes;
+  void* dy;
   int stop_layer;          // run layers 0..stop_layer (forward: L-1)
   Profiler* prof;
   double* s_out;           // feature export (may be null)
@@ -348,9 +362,49 @@ struct BackwardArgs {
   bool blend;
   double skip;
   const void* hw;
-  void* g_heads;
+  void* g_heads;            // wide branches: dE/dY, else (blended) dE_h/ds per (atom, head)
   Profiler* prof;
 };
+
+// ---- wide branch layers (branch.hip) --------------------------------------
+// Branches with a hidden layer this wide run as matrix products over tiles of
+// 128 rows; narrower ones (the single-head workloads' 32 to 128) stay in one
+// kernel per tile, whose weights are read from L2 cheaply.
+constexpr int BRANCH_WIDE = 256;
+inline bool branch_wide(const Hyper& hp) {
+  int w = 0;
+  for (size_t m = 0; m + 1 < hp.branch_dims.size(); ++m) w = w > hp.branch_dims[m] ? w : hp.branch_dims[m];
+  return w >= BRANCH_WIDE;
+}
+// width of Y, the branches' input (the last shared layer, or s)
+inline int branch_ky(const Hyper& hp) { return hp.shared_dims.empty() ? hp.F : pad32(hp.shared_dims.back()); }
+// Small batches take tiles of 32 rows: with 128 rows a batch of this many
+// atoms leaves most CUs without a tile.
+constexpr int BRANCH_SMALL_ATOMS = 4096;
+// Scratch the runtime provides for wide branches where it allocates freely.
+constexpr size_t BRANCH_SCRATCH_TARGET = (size_t)1 << 30;
+struct BranchArgs {
+  const PrecModel* pm;
+  const std::vector<int>* branch_dims;
+  int N, H;
+  bool small;                // tiles of 32 rows
+  long long max_tiles;       // upper bound of the tiles (the plan has the count)
+  const HeadTile* tiles;     // null: tiles of consecutive atoms, head 0
+  const HeadPlan* plan;
+  const int32_t* order;
+  const void* y;             // Y [N][planes][ky], storage type
+  int ky;
+  void* e;                   // [N]
+  void* eh;                  // [N][H]: blended heads, or null
+  void* dy;                  // null: energies only
+  void* scratch;
+  size_t scratch_bytes;
+};
+int branch_op_buffers(int nh, bool grad);
+// scratch bytes of one tile
+size_t branch_tile_bytes(int prec, const std::vector<int>& branch_dims, bool grad, bool small);
+hipError_t launch_branch(hipStream_t s, int prec, const BranchArgs& b);
+hipError_t launch_branch_rows(hipStream_t s, int prec, int N, int F, const void* src, void* y);
 hipError_t launch_backward(hipStream_t s, int prec, BackwardArgs& a);
 // The fixed scratch of painn_forward_noalloc: its size, the once-per-device
 // lookup of its address (painn_create calls it with the device current) and
@@ -363,8 +417,6 @@ void* noalloc_scratch(int device);
 constexpr int HB_GRID = 2048;
 // the sender-grouped edge list of a graph
 hipError_t launch_transpose(hipStream_t s, Profiler* p, painn_graph* g);
-size_t forward_workspace_bytes(int prec, int N, long long E, int F, int kcols, int B, int H,
-                               int S, bool blend);
 hipError_t launch_forward(hipStream_t s, int prec, ForwardArgs& a);
 // pm->h0 from pm->emb and layer 0's phi (enqueued on s; out holds
 // n_species x 3F storage elements)

@@ -39,6 +39,20 @@ __device__ __forceinline__ bf16_t f_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
+// The three bf16 planes of an FP32 value (upper 16 bits each).  A NaN keeps
+// its hi plane (quiet), an infinity too; their lower planes are zero.
+__device__ __forceinline__ void split3(float x, uint32_t* p) {
+  const uint32_t u = __float_as_uint(x);
+  const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+  const uint32_t h = u & 0xffff0000u;
+  const float r1 = x - __uint_as_float(h);
+  const uint32_t m = __float_as_uint(r1) & 0xffff0000u;
+  const float r2 = r1 - __uint_as_float(m);
+  p[0] = fin ? h : (h | ((u & 0x007fffffu) ? 0x00400000u : 0u));
+  p[1] = fin ? m : 0u;
+  p[2] = fin ? __float_as_uint(r2) & 0xffff0000u : 0u;
+}
+
 struct P64 {
   using T = double;  // storage
   using A = double;  // accumulation

@@ -8,6 +8,7 @@
 #include <fstream>
 #include <new>
 
+#include "branchgemm.h"
 #include "internal.h"
 
 namespace {
@@ -141,6 +142,88 @@ hipError_t pack_dense(PrecModel* pm, int prec, const double* W, const double* b,
   return upload(pm, bh, &out->b);
 }
 
+// Pack W [dout][din] for the branch products (branchgemm.h); tr: its transpose.
+hipError_t pack_branch(PrecModel* pm, int prec, const double* W, int dout, int din, bool tr, void** out) {
+  const int KB = branch_kb(prec), NP = branch_planes(prec), KPL = KB / 4;
+  const int no = tr ? din : dout, ni = tr ? dout : din;
+  const int nft = pad32(no) / 16, nkb = pad32(ni) / KB;
+  std::vector<unsigned char> wh(branch_pack_bytes(prec, no, ni), 0);
+  for (int ft = 0; ft < nft; ++ft)
+    for (int kb = 0; kb < nkb; ++kb)
+      for (int l = 0; l < 64; ++l)
+        for (int e = 0; e < KPL; ++e) {
+          const int o = 16 * ft + branch_feature(prec, l % 16), k = KB * kb + KPL * (l / 16) + e;
+          if (o >= no || k >= ni) continue;
+          const double x = tr ? W[(size_t)k * din + o] : W[(size_t)o * din + k];
+          const size_t blk = ((size_t)ft * nkb + kb) * NP;
+          if (prec == PAINN_FP64) {
+            memcpy(&wh[blk * 1024 + (size_t)l * 16 + e * 8], &x, 8);
+          } else if (prec == PAINN_FP32) {
+            // the three exact planes of the FP32 weight (as split3)
+            float r = (float)x;
+            for (int p = 0; p < 3; ++p) {
+              uint32_t u;
+              memcpy(&u, &r, 4);
+              u &= 0xffff0000u;
+              const uint16_t hi = (uint16_t)(u >> 16);
+              memcpy(&wh[(blk + p) * 1024 + (size_t)l * 16 + e * 2], &hi, 2);
+              float f;
+              memcpy(&f, &u, 4);
+              r -= f;
+            }
+          } else {
+            const bf16_t h = to_bf16(x);
+            memcpy(&wh[blk * 1024 + (size_t)l * 16 + e * 2], &h, 2);
+          }
+        }
+  return upload(pm, wh, out);
+}
+
+// The pointer table of the wide branches: [head][layer][4] = (w, bias, w^T,
+// plain row 0).  `with_T` adds the transposed hidden layers (forces).
+hipError_t build_branch_table(const painn_model* m, PrecModel* pm, bool with_T) {
+  const Hyper& hp = m->hp;
+  const int prec = pm->prec, nb = (int)hp.branch_dims.size();
+  const size_t nt = (size_t)hp.n_heads * nb * 4;
+  if (pm->branch_ptrs.empty()) pm->branch_ptrs.assign(nt, nullptr);
+  const double* M = m->master.data();
+  size_t idx = 1 + (size_t)A_PER_LAYER * hp.L + 2 * hp.shared_dims.size();
+  const int d0 = hp.shared_dims.empty() ? hp.F : hp.shared_dims.back();
+  hipError_t e = hipSuccess;
+  for (int h = 0; h < hp.n_heads && e == hipSuccess; ++h) {
+    int di = d0;
+    for (int mm = 0; mm < nb && e == hipSuccess; ++mm, idx += 2) {
+      const double* W = M + m->offsets[idx];
+      const double* b = M + m->offsets[idx + 1];
+      const int dout = hp.branch_dims[mm];
+      void** slot = &pm->branch_ptrs[((size_t)h * nb + mm) * 4];
+      const bool hidden = mm + 1 < nb;
+      if (hidden && !slot[0]) e = pack_branch(pm, prec, W, dout, di, false, &slot[0]);
+      if (e == hipSuccess && !slot[1]) {
+        std::vector<unsigned char> bh((size_t)pad32(dout) * acc_bytes(prec), 0);
+        for (int r = 0; r < dout; ++r) put_acc(bh, r, stored(b[r], prec), prec);
+        e = upload(pm, bh, &slot[1]);
+      }
+      if (e == hipSuccess && hidden && with_T && !slot[2]) e = pack_branch(pm, prec, W, dout, di, true, &slot[2]);
+      if (e == hipSuccess && !hidden && !slot[3]) {
+        std::vector<unsigned char> wh((size_t)pad32(di) * acc_bytes(prec), 0);
+        for (int k = 0; k < di; ++k) put_acc(wh, k, stored(W[k], prec), prec);
+        e = upload(pm, wh, &slot[3]);
+      }
+      di = dout;
+    }
+  }
+  if (e != hipSuccess) return e;
+  std::vector<unsigned char> tab(nt * sizeof(void*));
+  memcpy(tab.data(), pm->branch_ptrs.data(), tab.size());
+  void* dev = nullptr;
+  e = upload(pm, tab, &dev);
+  if (e != hipSuccess) return e;
+  pm->branch_table = dev;
+  pm->branch_stride = 4 * nb;
+  return hipSuccess;
+}
+
 void free_prec(PrecModel* pm) {
   if (!pm) return;
   for (void* p : pm->allocs) (void)hipFree(p);
@@ -221,8 +304,14 @@ painn_status build_prec(painn_model* m, int prec, PrecModel** out) {
     din = hp.shared_dims[mm];
     idx += 2;
   }
+  const bool wide_branch = branch_wide(hp);
+  if (wide_branch && e == hipSuccess) e = build_branch_table(m, pm, false);
   pm->branch.resize(hp.n_heads);
   for (int h = 0; h < hp.n_heads && e == hipSuccess; ++h) {
+    if (wide_branch) {
+      idx += 2 * hp.branch_dims.size();
+      continue;
+    }
     int di = din;
     for (size_t mm = 0; mm < hp.branch_dims.size() && e == hipSuccess; ++mm) {
       DenseDev d;
@@ -232,7 +321,7 @@ painn_status build_prec(painn_model* m, int prec, PrecModel** out) {
       idx += 2;
     }
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !wide_branch) {
     const size_t nb = hp.branch_dims.size();
     std::vector<unsigned char> tab((size_t)hp.n_heads * nb * 2 * sizeof(void*));
     void** tp = (void**)tab.data();
@@ -289,25 +378,46 @@ painn_status parse_model(painn_ctx* ctx, const unsigned char* buf, size_t n, pai
 
 }  // namespace
 
-// Workspace of one forward pass, carved in this order: s [N][F], v[0], v[1],
-// h [N][3F] (storage type), e [N] (accumulation type), the radial basis rows
-// [E + 16][kcols] (storage type), the edge info [E][4] (accumulation type),
-// then the head binning: plan (1 KiB), tiles [N M / 16 + 65][4] and the
-// (atom, head) order [N M] (int32), with M = 1 entry per atom (one dataset's
-// head) or M = H (blended heads); blended heads add the composition
-// [B][pad32(S)] (storage type), the head weights [B][H] and the per-head atom
-// energies [N][H] (accumulation type).
+// Workspace of one forward pass, carved in this order: s [N][F] (storage
+// type), e [N] (accumulation type), the edge info [E][4] (accumulation type),
+// the FP64 filter image, the head binning: plan (1 KiB), tiles
+// [N M / 16 + 65][4] and the (atom, head) order [N M] (int32), with M = 1
+// entry per atom (one dataset's head) or M = H (blended heads); blended heads
+// add the composition [B][pad32(S)] (storage type), the head weights [B][H]
+// and the per-head atom energies [N][H] (accumulation type).  Last the
+// buffers that nothing reads once the layers have run: v[0], v[1], h [N][3F]
+// and the radial basis rows [E + 16][kcols] (storage type); wide branches
+// take their place with Y and the branch layers' scratch.
 static size_t head_tiles_bytes(size_t entries) { return (entries / 16 + 65) * 16; }
 
-size_t forward_workspace_bytes(int prec, int N, long long E, int F, int kcols, int B, int H,
-                               int S, bool blend) {
+struct ForwardSpace {
+  size_t head, tail;     // bytes before and in the buffers that end with the layers
+  size_t tail_min;       // the tail wide branches cannot do without (Y and one tile)
+  size_t tail_full;      // the tail that takes all their tiles, or BRANCH_SCRATCH_TARGET, at once
+};
+
+static ForwardSpace forward_space(int prec, const Hyper& hp, int N, long long E, int kcols, int B, bool blend,
+                                  bool grad) {
   const size_t eb = elem_bytes(prec), ab = acc_bytes(prec);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t n = (size_t)N, ne = (size_t)E, ent = n * (blend ? (size_t)H : 1);
-  size_t b = al(n * F * eb) + 3 * al(n * 3 * F * eb) + al(n * ab) + al((ne + 16) * kcols * eb) +
-             al(ne * 4 * ab) + al(1024) + al(head_tiles_bytes(ent)) + al(ent * 4) + al(MSG64_IMAGE_BYTES);
-  if (blend) b += al((size_t)B * pad32(S) * eb) + al((size_t)B * H * ab) + al(n * H * ab);
-  return b;
+  const size_t n = (size_t)N, ne = (size_t)E, F = hp.F, H = hp.n_heads, ent = n * (blend ? H : 1);
+  ForwardSpace w;
+  w.head = al(n * F * eb) + al(n * ab) + al(ne * 4 * ab) + al(1024) + al(head_tiles_bytes(ent)) + al(ent * 4) +
+           al(MSG64_IMAGE_BYTES);
+  if (blend) w.head += al((size_t)B * pad32(hp.n_species) * eb) + al((size_t)B * H * ab) + al(n * H * ab);
+  w.tail = w.tail_min = w.tail_full = 3 * al(n * 3 * F * eb) + al((ne + 16) * kcols * eb);
+  if (branch_wide(hp)) {
+    const bool small = N < BRANCH_SMALL_ATOMS;
+    const size_t y = al(n * branch_row_bytes(prec, branch_ky(hp)));
+    const size_t t1 = branch_tile_bytes(prec, hp.branch_dims, grad, small);
+    const size_t tiles = ent / (small ? BRANCH_TM_SMALL : BRANCH_TM) + H;
+    size_t all = tiles * t1;
+    if (all > BRANCH_SCRATCH_TARGET) all = BRANCH_SCRATCH_TARGET;
+    if (all < t1) all = t1;
+    if (w.tail_min < y + t1) w.tail_min = y + t1;
+    if (w.tail_full < y + all) w.tail_full = y + all;
+  }
+  return w;
 }
 
 
@@ -716,7 +826,7 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
                                 double* energies, double* s_out, double* v_out, bool blend = false,
                                 double skip = 0.0, double* weights_out = nullptr, void* save = nullptr,
                                 ForwardArgs* keep = nullptr, void* ws_fixed = nullptr,
-                                size_t ws_fixed_bytes = 0) {
+                                size_t ws_fixed_bytes = 0, void* dy = nullptr) {
   if (!ctx) return PAINN_E_ARG;
   ctx->err.clear();
   if (!model || !g) return fail(ctx, PAINN_E_ARG, "null model or graph");
@@ -741,28 +851,39 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
   }
   const LayerDev& L0 = m->prec[prec]->layers[0];
   const int kcols = L0.filt_mma.din_p > L0.filt_nb.din_p ? L0.filt_mma.din_p : L0.filt_nb.din_p;
-  size_t need = forward_workspace_bytes(prec, g->N, g->E, m->hp.F, kcols, g->B, m->hp.n_heads,
-                                       m->hp.n_species, blend);
+  const ForwardSpace sp = forward_space(prec, m->hp, g->N, g->E, kcols, g->B, blend, dy != nullptr);
+  const size_t need = sp.head + sp.tail_min;
+  const size_t full = ctx->ws_tight ? need : sp.head + sp.tail_full;
   void* ws = ctx->ws;
+  size_t ws_total = ws_fixed_bytes;
   if (ws_fixed) {
     if (need > ws_fixed_bytes)
       return fail(ctx, PAINN_E_ARG, "this batch needs " + std::to_string(need) +
                                         " bytes of workspace; painn_forward_noalloc has " +
                                         std::to_string(ws_fixed_bytes));
     ws = ws_fixed;
-  } else if (need > ctx->ws_bytes) {
+  } else if (full > ctx->ws_bytes) {
     if (ctx->ws) {
       (void)hipStreamSynchronize(ctx->stream);
       (void)hipFree(ctx->ws);
       ctx->ws = nullptr;
       ctx->ws_bytes = 0;
     }
-    size_t want = need + need / 4;
+    const size_t slack = need + need / 4;
+    size_t want = slack > full ? slack : full;
     hipError_t e = hipMalloc(&ctx->ws, want);
+    if (e != hipSuccess && full > need) {
+      // without the full branch scratch the branches run in more chunks
+      (void)hipGetLastError();
+      ctx->ws_tight = true;
+      want = slack;
+      e = hipMalloc(&ctx->ws, want);
+    }
     if (e != hipSuccess) return fail(ctx, PAINN_E_OOM, "forward workspace allocation failed");
     ctx->ws_bytes = want;
     ws = ctx->ws;
   }
+  if (!ws_fixed) ws_total = ctx->ws_bytes;
   ForwardArgs a{};
   a.m = m;
   a.pm = m->prec[prec];
@@ -780,11 +901,7 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   char* p = (char*)ws;
   a.s = p; p += al(N * F * eb);
-  a.v[0] = p; p += al(N * 3 * F * eb);
-  a.v[1] = p; p += al(N * 3 * F * eb);
-  a.h = p; p += al(N * 3 * F * eb);
   a.e = p; p += al(N * ab);
-  a.basis = p; p += al(((size_t)g->E + 16) * kcols * eb);
   a.einfo = p; p += al((size_t)g->E * 4 * ab);
   a.msg_img = p; p += al(MSG64_IMAGE_BYTES);
   const size_t ent = N * (blend ? (size_t)m->hp.n_heads : 1);
@@ -801,6 +918,13 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
     a.hw = p; p += al((size_t)g->B * H * ab);
     a.eh = p; p += al(N * H * ab);
   }
+  a.branch_scratch = p;
+  a.branch_scratch_bytes = ws_total - (size_t)(p - (char*)ws);
+  a.dy = dy;
+  a.v[0] = p; p += al(N * 3 * F * eb);
+  a.v[1] = p; p += al(N * 3 * F * eb);
+  a.h = p; p += al(N * 3 * F * eb);
+  a.basis = p;
   if (keep) *keep = a;
   if (g->B == 0 && !s_out) return PAINN_OK;
   (void)hipGetLastError();   // do not report an error left by earlier, unrelated calls
@@ -818,7 +942,8 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
 // channels), per-atom scratch, per-edge dE/dr.
 static int forces_scratch_width(const Hyper& hp) {
   int zw = 0;
-  const int nl = (int)(hp.shared_dims.size() + hp.branch_dims.size());
+  // (wide branches keep their pre-activations in the branch scratch)
+  const int nl = (int)(hp.shared_dims.size() + (branch_wide(hp) ? 1 : hp.branch_dims.size()));
   for (int m = 0; m + 1 < nl; ++m)
     zw += pad32(m < (int)hp.shared_dims.size() ? hp.shared_dims[m]
                                                : hp.branch_dims[m - hp.shared_dims.size()]);
@@ -830,14 +955,15 @@ static int forces_scratch_width(const Hyper& hp) {
 // F = 384), [2][16][widest head layer + 2] per heads workgroup.
 static size_t forces_xbuf_bytes(int prec, const Hyper& hp, int N, bool blend) {
   const size_t eb = elem_bytes(prec), F = hp.F, tiles = ((size_t)N + 15) / 16;
-  const size_t head_tiles = ((size_t)N * (blend ? hp.n_heads : 1) + 15) / 16;
+  const bool wide = branch_wide(hp);
+  const size_t head_tiles = ((size_t)N * (blend && !wide ? hp.n_heads : 1) + 15) / 16;
   // LDS row padding of the dense kernels' activation tiles (elements)
   const size_t pad = lds_pad(prec);
   size_t x = 0;
   if (16 * (4 * F + 2 * pad) * eb > 160 * 1024) x = tiles * 16 * (3 * F + pad) * eb;
   int wmax = hp.F;
   for (int d : hp.shared_dims) wmax = wmax > pad32(d) ? wmax : pad32(d);
-  for (size_t mm = 0; mm + 1 < hp.branch_dims.size(); ++mm)
+  for (size_t mm = 0; mm + 1 < hp.branch_dims.size() && !wide; ++mm)
     wmax = wmax > pad32(hp.branch_dims[mm]) ? wmax : pad32(hp.branch_dims[mm]);
   const size_t hb = (size_t)2 * 16 * (wmax + pad) * eb;
   if (hb > 150 * 1024) {
@@ -853,10 +979,16 @@ static size_t forces_scratch_rows(int N) {
   return (size_t)N > (size_t)HB_GRID * 16 ? (size_t)N : (size_t)HB_GRID * 16;
 }
 
+// dE/dY per atom or (atom, head) with wide branches; else, blended, dE_h/ds.
+static size_t forces_gheads_bytes(int prec, const Hyper& hp, int N, bool blend) {
+  const size_t rows = (size_t)N * (blend ? hp.n_heads : 1) * acc_bytes(prec);
+  return branch_wide(hp) ? rows * branch_ky(hp) : blend ? rows * hp.F : 0;
+}
+
 static size_t forces_workspace_bytes(int prec, const Hyper& hp, int N, long long E, int kcols, bool blend) {
   const size_t eb = elem_bytes(prec), ab = acc_bytes(prec), n = (size_t)N, F = hp.F;
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  return al(forces_xbuf_bytes(prec, hp, N, blend)) + al(blend ? n * hp.n_heads * F * ab : 0) +
+  return al(forces_xbuf_bytes(prec, hp, N, blend)) + al(forces_gheads_bytes(prec, hp, N, blend)) +
          al(SaveLayout::bytes(n, F, hp.L, eb)) + 2 * al(n * F * ab) + 3 * al(n * 3 * F * ab) +
          2 * al(((size_t)E + 16) * kcols * eb) + al((size_t)E * 4 * ab) + al((size_t)E * (F / 16) * 4 * ab) +
          al(forces_scratch_rows(N) * forces_scratch_width(hp) * ab) + al((size_t)E * 3 * sizeof(double));
@@ -906,7 +1038,9 @@ static painn_status build_prec_T(painn_model* m, PrecModel* pm) {
   }
   pm->branchT.assign(hp.n_heads, {});
   const size_t nb = hp.branch_dims.size();
-  for (int h = 0; h < hp.n_heads && e == hipSuccess; ++h) {
+  const bool wide_branch = pm->branch_table != nullptr;
+  if (wide_branch && e == hipSuccess) e = build_branch_table(m, pm, true);
+  for (int h = 0; h < hp.n_heads && e == hipSuccess && !wide_branch; ++h) {
     int di = din;
     for (size_t mm = 0; mm < nb && e == hipSuccess; ++mm) {
       DenseDev d;
@@ -916,7 +1050,7 @@ static painn_status build_prec_T(painn_model* m, PrecModel* pm) {
       idx += 2;
     }
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !wide_branch) {
     std::vector<unsigned char> tab((size_t)hp.n_heads * nb * 2 * sizeof(void*), 0);
     void** tp = (void**)tab.data();
     for (int h = 0; h < hp.n_heads; ++h)
@@ -997,7 +1131,7 @@ static painn_status forces_impl(painn_ctx* ctx, const painn_model* model, const 
   BackwardArgs b{};
   b.xbuf_bytes = forces_xbuf_bytes(precision, hp, g->N, blend);
   b.xbuf = p; p += al(b.xbuf_bytes);
-  b.g_heads = p; p += al(blend ? N * hp.n_heads * F * ab : 0);
+  b.g_heads = p; p += al(forces_gheads_bytes(precision, hp, g->N, blend));
   b.save = p; p += al(SaveLayout::bytes(N, F, hp.L, eb));
   b.gs = p; p += al(N * F * ab);
   b.gs2 = p; p += al(N * F * ab);
@@ -1013,7 +1147,7 @@ static painn_status forces_impl(painn_ctx* ctx, const painn_model* model, const 
   b.gr = (double*)p;
   ForwardArgs fa{};
   painn_status st = run_forward(ctx, model, graph, dataset_id, precision, hp.L - 1, energies, nullptr, nullptr,
-                                blend, skip, weights, b.save, &fa);
+                                blend, skip, weights, b.save, &fa, nullptr, 0, branch_wide(hp) ? b.g_heads : nullptr);
   if (st != PAINN_OK) return st;
   b.m = m;
   b.pm = pm;
