@@ -1638,27 +1638,38 @@ __global__ void __launch_bounds__(256) k_edge_grad(long long E, int NW, const in
   gr[3 * e + 2] = gd * uz + (gz - dot * uz) / d;
 }
 
+// 16 lanes per atom, each on every 16th edge of the atom's two lists, then a
+// butterfly over them: a fixed order.  (One thread per atom walked up to 150
+// edges one load at a time: 105 us for 14,000 atoms of 72 neighbours.)
+constexpr int FORCE_LANES = 16;
 __global__ void __launch_bounds__(256) k_forces(int N, const int32_t* __restrict__ row_ptr,
                                                const int32_t* __restrict__ t_ptr,
                                                const int32_t* __restrict__ t_edge,
                                                const double* __restrict__ gr, double* __restrict__ forces) {
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
+  const int a = blockIdx.x * (256 / FORCE_LANES) + threadIdx.x / FORCE_LANES, l = threadIdx.x % FORCE_LANES;
   if (a >= N) return;
   double fx = 0, fy = 0, fz = 0;
-  for (int e = row_ptr[a]; e < row_ptr[a + 1]; ++e) {
+  for (int e = row_ptr[a] + l; e < row_ptr[a + 1]; e += FORCE_LANES) {
     fx += gr[3 * (size_t)e];
     fy += gr[3 * (size_t)e + 1];
     fz += gr[3 * (size_t)e + 2];
   }
-  for (int t = t_ptr[a]; t < t_ptr[a + 1]; ++t) {
+  for (int t = t_ptr[a] + l; t < t_ptr[a + 1]; t += FORCE_LANES) {
     const size_t e = t_edge[t];
     fx -= gr[3 * e];
     fy -= gr[3 * e + 1];
     fz -= gr[3 * e + 2];
   }
-  forces[3 * (size_t)a] = fx;
-  forces[3 * (size_t)a + 1] = fy;
-  forces[3 * (size_t)a + 2] = fz;
+  for (int off = FORCE_LANES / 2; off; off >>= 1) {
+    fx += __shfl_xor(fx, off);
+    fy += __shfl_xor(fy, off);
+    fz += __shfl_xor(fz, off);
+  }
+  if (l == 0) {
+    forces[3 * (size_t)a] = fx;
+    forces[3 * (size_t)a + 1] = fy;
+    forces[3 * (size_t)a + 2] = fz;
+  }
 }
 
 // ---------------------------------------------------------------- driver ----
@@ -1882,7 +1893,7 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
   if (E > 0)
     k_edge_grad<A><<<(unsigned)((E + 255) / 256), 256, 0, st>>>(E, NW, g->recv, g->col, g->shift, g->atom_struct,
                                                                  g->pos, g->cell, (const A*)ba.eg, ba.gr);
-  k_forces<<<(N + 255) / 256, 256, 0, st>>>(N, g->row_ptr, g->t_ptr, g->t_edge, ba.gr, ba.forces);
+  k_forces<<<(N + 256 / FORCE_LANES - 1) / (256 / FORCE_LANES), 256, 0, st>>>(N, g->row_ptr, g->t_ptr, g->t_edge, ba.gr, ba.forces);
   prof_mark(ba.prof, st, KC_FORCE, false);
   return hipGetLastError();
 }

@@ -1295,14 +1295,19 @@ __global__ void __launch_bounds__(64 * NW) k_heads(HeadArgs a) {
 }
 
 // ------------------------------------------------------------ energies ----
+// One wave per structure: lane l sums atoms l, l + 64, ... and a butterfly
+// adds the lanes, a fixed order.  (One thread per structure walked its atoms
+// one load at a time: 31 us for 1,255 structures of up to 200 atoms, 91 us
+// for 1,024 of up to 256, a serial chain on a handful of workgroups.)
 template <class A>
 __global__ void __launch_bounds__(256) k_energy(int B, const int32_t* __restrict__ struct_ptr,
                                                const A* __restrict__ e, double* __restrict__ E) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (b >= B) return;
   double acc = 0.0;
-  for (int i = struct_ptr[b]; i < struct_ptr[b + 1]; ++i) acc += (double)e[i];
-  E[b] = acc;
+  for (int i = struct_ptr[b] + lane; i < struct_ptr[b + 1]; i += 64) acc += (double)e[i];
+  for (int off = 32; off; off >>= 1) acc += __shfl_xor(acc, off);
+  if (lane == 0) E[b] = acc;
 }
 
 // s [N][Fl] and v [N][3][Fl] in FP64 from the working arrays of width F >= Fl
@@ -2151,7 +2156,7 @@ hipError_t forward_impl(hipStream_t st, ForwardArgs& fa) {
     if (e != hipSuccess) return e;
   }
   prof_mark(fa.prof, st, KC_ENERGY, true);
-  k_energy<A><<<(g->B + 255) / 256, 256, 0, st>>>(g->B, g->struct_ptr, (const A*)fa.e, fa.energies);
+  k_energy<A><<<(g->B + 3) / 4, 256, 0, st>>>(g->B, g->struct_ptr, (const A*)fa.e, fa.energies);
   prof_mark(fa.prof, st, KC_ENERGY, false);
   return hipGetLastError();
 }
