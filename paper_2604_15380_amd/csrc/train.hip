@@ -23,8 +23,8 @@
 // Weights live in one flat FP64 array in the weight file's order at the
 // model's own width F.  Every weight gradient is a reduction over atoms or
 // edges computed by one launch in a fixed order (no atomics), so a step is
-// deterministic.  The kernels are plain FP64 vector-ALU code with LDS tiles:
-// a training batch of the lead model (25 structures) is small.
+// deterministic.  The dense layers and weight gradients run on the FP64 matrix
+// cores.
 #include <math.h>
 #include <string.h>
 
@@ -97,52 +97,95 @@ inline unsigned blocks(size_t n, int t = TB) { return (unsigned)((n + t - 1) / t
 constexpr int WG_CHUNKS = 32;
 
 // ---- dense layers ------------------------------------------------------------
+// FP64 matrix-core tiles (v_mfma_f64_16x16x4f64: lane l holds A row l % 16 and
+// B column l % 16 at k = l / 16; result register i of lane l is row
+// 4 i + l / 16, column l % 16).  A training batch is small (2,171 atoms in 25
+// structures of the lead model), so what bounds these layers is how many
+// workgroups a launch brings and the launches themselves: a tile is 32 rows x
+// 64 columns (408 workgroups for N = 2,171 and F = 337), and the branches of
+// all heads go out in one launch (gridDim.z; one launch per head ran 125
+// workgroups of 776 / 32 steps one after the other).  The vector-ALU form of
+// these tiles took 65 us per branch layer and head.
+typedef double d4_t __attribute__((ext_vector_type(4)));
+constexpr int TD_R = 32, TD_C = 64, TD_K = 32, TD_LD = 34;   // LD: a half wave's 16 x 2 reads in distinct banks
+
+__device__ __forceinline__ double comp(double x, int) { return x; }
+__device__ __forceinline__ double comp(Dual x, int c) { return c ? x.d : x.v; }
+
 // Y[r][o] = sum_k X[r][k] W(o, k) (+ b[o] on the value part) (+ ADD[r][o]),
 // W(o, k) = W[o * wo + k * wk] (wo = din, wk = 1 for a layer stored
 // [out, in]; wo = 1, wk = dout_of_the_layer for its transpose); with SILU,
-// Z keeps the pre-activation and Y = silu(Z).  Rows [lo, hi) with lo, hi from
-// `range` (device) when given, else [0, rows).  32 x 32 output tiles, 2 x 2 per
-// thread, k in steps of 32 through LDS.
+// Z keeps the pre-activation and Y = silu(Z).  Head blockIdx.z takes its
+// weights hs elements further each; rows [lo, hi) with lo, hi from
+// range + blockIdx.z (device) when given, else [0, rows).
 template <class S, bool SILU>
 __global__ void __launch_bounds__(256) k_tr_dense(int rows, const int32_t* __restrict__ range, int din, int dout,
                                                   const S* __restrict__ X, int ldx, const double* __restrict__ W,
-                                                  long long wo, long long wk, const double* __restrict__ b,
-                                                  const S* __restrict__ add, int ldadd, S* __restrict__ Z,
-                                                  S* __restrict__ Y, int ldy) {
-  __shared__ S Xs[32][33];
-  __shared__ double Ws[32][33];
-  const int lo = range ? range[0] : 0, hi = range ? range[1] : rows;
-  const int r0 = lo + blockIdx.x * 32, o0 = blockIdx.y * 32;
+                                                  long long wo, long long wk, long long hs,
+                                                  const double* __restrict__ b, const S* __restrict__ add, int ldadd,
+                                                  S* __restrict__ Z, S* __restrict__ Y, int ldy) {
+  constexpr int NC = sizeof(S) / sizeof(double);     // value (and tangent)
+  __shared__ double Xs[NC][TD_R * TD_LD], Ws[TD_C * TD_LD];
+  const int lo = range ? range[blockIdx.z] : 0, hi = range ? range[blockIdx.z + 1] : rows;
+  const int r0 = lo + blockIdx.x * TD_R, o0 = blockIdx.y * TD_C;
   if (r0 >= hi) return;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  S acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = cst<S>(0.0);
-  for (int k0 = 0; k0 < din; k0 += 32) {
-    for (int q = threadIdx.x; q < 1024; q += 256) {
-      const int rr = q >> 5, kk = q & 31, r = r0 + rr, k = k0 + kk;
-      Xs[rr][kk] = (r < hi && k < din) ? X[(size_t)r * ldx + k] : cst<S>(0.0);
-      const int o = o0 + rr;
-      Ws[rr][kk] = (o < dout && k < din) ? W[(long long)o * wo + (long long)k * wk] : 0.0;
+  W += (long long)blockIdx.z * hs;
+  if (b) b += (long long)blockIdx.z * hs;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NX = TD_R * TD_K / 256, NW = TD_C * TD_K / 256;
+  S xr[NX];
+  double wr[NW];
+  const bool along_k = wk == 1;
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+      const int r = r0 + (tid >> 5) + 8 * q, k = k0 + (tid & 31);
+      xr[q] = (r < hi && k < din) ? X[(size_t)r * ldx + k] : cst<S>(0.0);
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 32; ++kk) {
-      const S x0 = Xs[2 * ty][kk], x1 = Xs[2 * ty + 1][kk];
-      const double w0 = Ws[2 * tx][kk], w1 = Ws[2 * tx + 1][kk];
-      acc[0][0] += x0 * w0;
-      acc[0][1] += x0 * w1;
-      acc[1][0] += x1 * w0;
-      acc[1][1] += x1 * w1;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const int o = o0 + (along_k ? (tid >> 5) + 8 * q : tid & 63), k = k0 + (along_k ? tid & 31 : (tid >> 6) + 4 * q);
+      wr[q] = (o < dout && k < din) ? W[(long long)o * wo + (long long)k * wk] : 0.0;
     }
+  };
+  d4_t acc[NC][2];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    for (int t = 0; t < 2; ++t) acc[c][t] = d4_t{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  for (int k0 = 0; k0 < din; k0 += TD_K) {
+    if (k0) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NX; ++q)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) Xs[c][((tid >> 5) + 8 * q) * TD_LD + (tid & 31)] = comp(xr[q], c);
+#pragma unroll
+    for (int q = 0; q < NW; ++q)
+      Ws[(along_k ? (tid >> 5) + 8 * q : tid & 63) * TD_LD + (along_k ? tid & 31 : (tid >> 6) + 4 * q)] = wr[q];
     __syncthreads();
+    if (k0 + TD_K < din) load(k0 + TD_K);
+    const double* wp = Ws + (16 * wave + (lane & 15)) * TD_LD + (lane >> 4);
+    const int xo = (lane & 15) * TD_LD + (lane >> 4);
+#pragma unroll
+    for (int kk = 0; kk < TD_K; kk += 4) {
+      const double w = wp[kk];
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          acc[c][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[c][xo + 16 * t * TD_LD + kk], w, acc[c][t], 0, 0, 0);
+    }
   }
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) {
-      const int r = r0 + 2 * ty + i, o = o0 + 2 * tx + j;
-      if (r >= hi || o >= dout) continue;
-      S y = acc[i][j];
-      if (b) y = y + b[o];
+  const int o = o0 + 16 * wave + (lane & 15);
+  if (o >= dout) return;
+  const double bias = b ? b[o] : 0.0;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 + 16 * t + 4 * i + (lane >> 4);
+      if (r >= hi) continue;
+      S y = mk<S>(acc[0][t][i] + bias, acc[NC - 1][t][i]);
       if (add) y = y + add[(size_t)r * ldadd + o];
       if (SILU) {
         Z[(size_t)r * ldy + o] = y;
@@ -152,53 +195,112 @@ __global__ void __launch_bounds__(256) k_tr_dense(int rows, const int32_t* __res
     }
 }
 
-// Weight gradient over rows [lo, hi): G[o][k] = part( sum_r sc[r] A[r][o] B[r][k] )
+// Weight gradient over rows [lo, hi): G[o][k] = tangent( sum_r sc[r] A[r][o] B[r][k] )
 // for k < din, and with a bias the column k = din, where B is taken as 1:
-// Gb[o] = part( sum_r sc[r] A[r][o] ) (sc may be null: 1).  The rows are cut
-// into gridDim.z chunks of `rch`; chunk z writes its partial sums to
-// Pz[z][o][kb] (kb < din + 1), and k_tr_wgrad_sum adds the chunks in order,
-// so the result does not depend on scheduling.
-template <class S>
+// Gb[o] = tangent( sum_r sc[r] A[r][o] ) (sc may be null: 1).  The tangent of a
+// product is A.v B.d + A.d B.v: two matrix products.  64 x 64 output tiles, a
+// 32 x 32 quarter per wave, 16 rows per step through LDS (the next 16 loaded
+// meanwhile).  One head's layer: gridDim.z cuts the rows into chunks of `rch`
+// whose partial sums go to Pz[z][o][kb] (kb < dinb), and k_tr_wgrad_sum adds
+// the chunks in order.  Several heads (hs > 0): gridDim.z is the head, whose
+// rows go through one workgroup per tile straight into G and Gb.  Either way
+// the result does not depend on scheduling.  Sums of 64 rows are added up
+// apart: one running sum over a head's hundreds of equal bias terms had four
+// times the rounding error.
+constexpr int TG_T = 64, TG_R = 16, TG_LD = 80;              // LD: 16 x 2 reads in distinct banks
 __global__ void __launch_bounds__(256) k_tr_wgrad(int rows, const int32_t* __restrict__ range, int dout, int din,
-                                                  int dinb, int rch, const S* __restrict__ A, int lda,
-                                                  const S* __restrict__ Bm, int ldb, const S* __restrict__ sc,
-                                                  double* __restrict__ Pz) {
-  __shared__ S As[32][33];
-  __shared__ S Bs[32][33];
-  const int lo0 = range ? range[0] : 0, hi0 = range ? range[1] : rows;
-  const int lo = lo0 + blockIdx.z * rch, hi = min(hi0, lo + rch);
-  const int k0 = blockIdx.x * 32, o0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  S acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = cst<S>(0.0);
-  for (int rb = lo; rb < hi; rb += 32) {
-    for (int q = threadIdx.x; q < 1024; q += 256) {
-      const int rr = q >> 5, cc = q & 31, r = rb + rr;
-      const int o = o0 + cc, k = k0 + cc;
-      S a = (r < hi && o < dout) ? A[(size_t)r * lda + o] : cst<S>(0.0);
-      if (sc && r < hi) a = a * sc[r];
-      As[rr][cc] = a;
-      Bs[rr][cc] = (r < hi && k < din) ? Bm[(size_t)r * ldb + k] : (r < hi && k == din) ? cst<S>(1.0) : cst<S>(0.0);
+                                                  int dinb, int rch, long long hs, const Dual* __restrict__ A,
+                                                  int lda, const Dual* __restrict__ Bm, int ldb,
+                                                  const Dual* __restrict__ sc, double* __restrict__ Pz,
+                                                  double* __restrict__ G, double* __restrict__ Gb) {
+  __shared__ double As[2][TG_R * TG_LD], Bs[2][TG_R * TG_LD];
+  const int head = hs ? blockIdx.z : 0, z = hs ? 0 : blockIdx.z;
+  const int lo0 = range ? range[head] : 0, hi0 = range ? range[head + 1] : rows;
+  const int lo = hs ? lo0 : lo0 + z * rch, hi = hs ? hi0 : min(hi0, lo + rch);
+  const int k0 = blockIdx.x * TG_T, o0 = blockIdx.y * TG_T;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NQ = TG_R * TG_T / 256;
+  Dual ar[NQ], br[NQ];
+  auto load = [&](int rb) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int r = rb + (tid >> 6) + 4 * q, o = o0 + (tid & 63), k = k0 + (tid & 63);
+      ar[q] = br[q] = Dual{0.0, 0.0};
+      if (r < hi) {
+        if (o < dout) ar[q] = A[(size_t)r * lda + o];
+        if (sc) ar[q] = ar[q] * sc[r];
+        if (k < din) br[q] = Bm[(size_t)r * ldb + k];
+        else if (k == din) br[q] = Dual{1.0, 0.0};
+      }
+    }
+  };
+  d4_t acc[2][2], sum[2][2];
+  for (int a = 0; a < 2; ++a)
+    for (int c = 0; c < 2; ++c) acc[a][c] = sum[a][c] = d4_t{0.0, 0.0, 0.0, 0.0};
+  auto flush = [&] {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        sum[a][c] += acc[a][c];
+        acc[a][c] = d4_t{0.0, 0.0, 0.0, 0.0};
+      }
+  };
+  if (lo < hi) load(lo);
+  for (int rb = lo; rb < hi; rb += TG_R) {
+    if (rb > lo) __syncthreads();
+    if (rb > lo && ((rb - lo) & 63) == 0) flush();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int x = ((tid >> 6) + 4 * q) * TG_LD + (tid & 63);
+      As[0][x] = ar[q].v;
+      As[1][x] = ar[q].d;
+      Bs[0][x] = br[q].v;
+      Bs[1][x] = br[q].d;
     }
     __syncthreads();
-#pragma unroll 8
-    for (int rr = 0; rr < 32; ++rr) {
-      const S a0 = As[rr][2 * ty], a1 = As[rr][2 * ty + 1];
-      const S b0 = Bs[rr][2 * tx], b1 = Bs[rr][2 * tx + 1];
-      acc[0][0] += a0 * b0;
-      acc[0][1] += a0 * b1;
-      acc[1][0] += a1 * b0;
-      acc[1][1] += a1 * b1;
+    if (rb + TG_R < hi) load(rb + TG_R);
+    const int ao = (lane >> 4) * TG_LD + 32 * (wave >> 1) + (lane & 15);
+    const int bo = (lane >> 4) * TG_LD + 32 * (wave & 1) + (lane & 15);
+#pragma unroll
+    for (int rr = 0; rr < TG_R; rr += 4) {
+      double av[2], ad[2], bv[2], bd[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        av[t] = As[0][ao + rr * TG_LD + 16 * t];
+        ad[t] = As[1][ao + rr * TG_LD + 16 * t];
+        bv[t] = Bs[0][bo + rr * TG_LD + 16 * t];
+        bd[t] = Bs[1][bo + rr * TG_LD + 16 * t];
+      }
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bd[c], acc[a][c], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[a], bv[c], acc[a][c], 0, 0, 0);
     }
-    __syncthreads();
   }
-  double* P = Pz + (size_t)blockIdx.z * dout * dinb;
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) {
-      const int o = o0 + 2 * ty + i, k = k0 + 2 * tx + j;
-      if (o < dout && k < dinb) P[(size_t)o * dinb + k] = part(acc[i][j]);
-    }
+  flush();
+  double* P = Pz ? Pz + (size_t)z * dout * dinb : nullptr;
+  if (!P) {
+    G += (long long)head * hs;
+    if (Gb) Gb += (long long)head * hs;
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = o0 + 32 * (wave >> 1) + 16 * a + 4 * i + (lane >> 4);
+        const int k = k0 + 32 * (wave & 1) + 16 * c + (lane & 15);
+        if (o >= dout || k >= dinb) continue;
+        if (P) P[(size_t)o * dinb + k] = sum[a][c][i];
+        else if (k < din) G[(size_t)o * din + k] = sum[a][c][i];
+        else Gb[o] = sum[a][c][i];
+      }
 }
 
 // G[o][k] = sum over the chunks z (in order) of Pz[z][o][k], k < din; the
@@ -525,25 +627,39 @@ __global__ void k_tr_upd_bwd2(int N, int F, const S* __restrict__ g_in, const S*
 // head): perm[p] = atom, hstart[h] = first slot of head h, hstart[H] = slots
 // in use; atoms of a structure whose id is outside [0, H) get no slot and
 // set *bad.
-__global__ void k_tr_group(int B, int H, const int32_t* __restrict__ struct_ptr,
-                           const int32_t* __restrict__ dataset_id, int32_t* __restrict__ perm,
-                           int32_t* __restrict__ hstart, int32_t* __restrict__ bad) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int slot = 0, nbad = 0;
-  for (int h = 0; h < H; ++h) {
-    hstart[h] = slot;
-    for (int b = 0; b < B; ++b) {
-      const int d = dataset_id ? dataset_id[b] : 0;
-      if (d != h) continue;
-      for (int a = struct_ptr[b]; a < struct_ptr[b + 1]; ++a) perm[slot++] = a;
+// One workgroup: every structure's first slot by counting the atoms before it
+// (first[b]), then the atoms in parallel.
+__global__ void __launch_bounds__(256) k_tr_group(int B, int N, int H, const int32_t* __restrict__ struct_ptr,
+                                                  const int32_t* __restrict__ atom_struct,
+                                                  const int32_t* __restrict__ dataset_id, int32_t* __restrict__ perm,
+                                                  int32_t* __restrict__ hstart, int32_t* __restrict__ bad,
+                                                  int32_t* __restrict__ first) {
+  __shared__ int nbad;
+  if (threadIdx.x == 0) nbad = 0;
+  __syncthreads();
+  // (head H stands for the end of the last one)
+  for (int x = threadIdx.x; x < B + H + 1; x += 256) {
+    const int b = x - (H + 1);
+    const int d = b < 0 ? x : dataset_id ? dataset_id[b] : 0;
+    int slot = 0;
+    for (int q = 0; q < B; ++q) {
+      const int dq = dataset_id ? dataset_id[q] : 0;
+      if (dq < 0 || dq >= H) continue;
+      if (dq < d || (dq == d && q < b)) slot += struct_ptr[q + 1] - struct_ptr[q];
+    }
+    if (b < 0) {
+      hstart[x] = slot;
+    } else {
+      first[b] = d < 0 || d >= H ? -1 : slot;
+      if (d < 0 || d >= H) atomicAdd(&nbad, 1);
     }
   }
-  hstart[H] = slot;
-  for (int b = 0; b < B; ++b) {
-    const int d = dataset_id ? dataset_id[b] : 0;
-    if (d < 0 || d >= H) ++nbad;
+  __syncthreads();
+  if (threadIdx.x == 0) *bad = nbad;
+  for (int a = threadIdx.x; a < N; a += 256) {
+    const int b = atom_struct[a], f = first[b];
+    if (f >= 0) perm[f + a - struct_ptr[b]] = a;
   }
-  *bad = nbad;
 }
 
 template <class S>
@@ -588,17 +704,23 @@ __global__ void k_tr_seed(int N, const int32_t* __restrict__ slots, const int32_
   g[p] = p < *slots ? mk<S>(1.0, c ? c[atom_struct[perm[p]]] : 0.0) : cst<S>(0.0);
 }
 
-// embedding gradient: G[z][f] = part(sum of g_s over the atoms of species z)
+// embedding gradient: G[z][f] = part(sum of g_s over the atoms of species z),
+// atoms in order; a workgroup takes one species and 256 features, the species
+// array comes through LDS 256 atoms at a time.
 template <class S>
-__global__ void k_tr_emb_grad(int N, int F, int n_species, const int32_t* __restrict__ species,
-                              const S* __restrict__ gs, double* __restrict__ G) {
-  const size_t idx = (size_t)blockIdx.x * TB + threadIdx.x;
-  if (idx >= (size_t)n_species * F) return;
-  const int z = (int)(idx / F), f = (int)(idx % F);
+__global__ void __launch_bounds__(256) k_tr_emb_grad(int N, int F, const int32_t* __restrict__ species,
+                                                     const S* __restrict__ gs, double* __restrict__ G) {
+  __shared__ int sp[256];
+  const int z = blockIdx.x, f = blockIdx.y * 256 + threadIdx.x;
   S acc = cst<S>(0.0);
-  for (int i = 0; i < N; ++i)
-    if (species[i] == z) acc += gs[(size_t)i * F + f];
-  G[idx] = part(acc);
+  for (int i0 = 0; i0 < N; i0 += 256) {
+    __syncthreads();
+    sp[threadIdx.x] = i0 + (int)threadIdx.x < N ? species[i0 + threadIdx.x] : -1;
+    __syncthreads();
+    for (int q = 0; q < 256; ++q)
+      if (sp[q] == z && f < F) acc += gs[(size_t)(i0 + q) * F + f];
+  }
+  if (f < F) G[(size_t)z * F + f] = part(acc);
 }
 
 // ---- loss and optimizer ----------------------------------------------------------
@@ -855,29 +977,38 @@ size_t carve(TrWs* w, char* base, const Hyper& hp, int N, long long E, int B) {
   return off;
 }
 
-dim3 dgrid(int rows, int dout) { return dim3((unsigned)((rows + 31) / 32), (unsigned)((dout + 31) / 32)); }
+dim3 dgrid(int rows, int dout, int heads = 1) {
+  return dim3((unsigned)((rows + TD_R - 1) / TD_R), (unsigned)((dout + TD_C - 1) / TD_C), (unsigned)heads);
+}
+
+// The heads of a grouped layer: `n` heads whose weights lie `stride` elements
+// apart; rows of head h: [range[h], range[h + 1]) of the grouped order.
+struct Heads {
+  int n = 1;
+  long long stride = 0;
+};
 
 // Y = X W^T + b for a layer stored [dout, din] at weight offset wofs
 template <class S>
 void dense(hipStream_t st, const double* th, int rows, const int32_t* range, int din, int dout, const S* X, int ldx,
-           size_t wofs, const size_t* bofs, bool silu_on, S* Z, S* Y, int ldy, const S* add = nullptr, int ldadd = 0) {
+           size_t wofs, const size_t* bofs, bool silu_on, S* Z, S* Y, int ldy, Heads hd = {}) {
   if (rows <= 0) return;
   const double* b = bofs ? th + *bofs : nullptr;
   if (silu_on)
-    k_tr_dense<S, true><<<dgrid(rows, dout), 256, 0, st>>>(rows, range, din, dout, X, ldx, th + wofs, din, 1, b, add,
-                                                           ldadd, Z, Y, ldy);
+    k_tr_dense<S, true><<<dgrid(rows, dout, hd.n), 256, 0, st>>>(rows, range, din, dout, X, ldx, th + wofs, din, 1,
+                                                                 hd.stride, b, nullptr, 0, Z, Y, ldy);
   else
-    k_tr_dense<S, false><<<dgrid(rows, dout), 256, 0, st>>>(rows, range, din, dout, X, ldx, th + wofs, din, 1, b,
-                                                            add, ldadd, nullptr, Y, ldy);
+    k_tr_dense<S, false><<<dgrid(rows, dout, hd.n), 256, 0, st>>>(rows, range, din, dout, X, ldx, th + wofs, din, 1,
+                                                                  hd.stride, b, nullptr, 0, nullptr, Y, ldy);
 }
 
 // GX = GY W (+ ADD) for a layer stored [dout, din]: GX [rows][din]
 template <class S>
 void dense_t(hipStream_t st, const double* th, int rows, const int32_t* range, int dout, int din, const S* GY, int ldgy,
-             size_t wofs, S* GX, int ldgx, const S* add = nullptr, int ldadd = 0) {
+             size_t wofs, S* GX, int ldgx, const S* add = nullptr, int ldadd = 0, Heads hd = {}) {
   if (rows <= 0) return;
-  k_tr_dense<S, false><<<dgrid(rows, din), 256, 0, st>>>(rows, range, dout, din, GY, ldgy, th + wofs, 1, din, nullptr,
-                                                         add, ldadd, nullptr, GX, ldgx);
+  k_tr_dense<S, false><<<dgrid(rows, din, hd.n), 256, 0, st>>>(rows, range, dout, din, GY, ldgy, th + wofs, 1, din,
+                                                               hd.stride, nullptr, add, ldadd, nullptr, GX, ldgx);
 }
 
 // Row chunks of a weight-gradient reduction over `rows` rows: at most
@@ -888,18 +1019,22 @@ inline int wg_chunks(long long rows) {
 }
 
 // Weight (and bias) gradient of a layer stored [dout, din] at wofs (bias at
-// *bofs), reducing over the rows [lo, hi) of A and B (range on the device, or
-// all `rows`); `rows` bounds the row count used to cut the chunks.
-template <class S>
+// *bofs), reducing over `rows` rows of A and B, or of each of several heads
+// over its range.
 void wgrad(hipStream_t st, double* G, double* scratch, int rows, const int32_t* range, int dout, int din,
-           const S* A, int lda, const S* Bm, int ldb, size_t wofs, const size_t* bofs, const S* sc = nullptr) {
+           const Dual* A, int lda, const Dual* Bm, int ldb, size_t wofs, const size_t* bofs, const Dual* sc = nullptr,
+           Heads hd = {}) {
   const int dinb = din + (bofs ? 1 : 0);
-  const int nz = wg_chunks(rows);
+  const int nz = hd.n > 1 ? 1 : wg_chunks(rows);
   const int rch = (rows + nz - 1) / nz;
-  k_tr_wgrad<S><<<dim3((unsigned)((dinb + 31) / 32), (unsigned)((dout + 31) / 32), (unsigned)nz), 256, 0, st>>>(
-      rows, range, dout, din, dinb, rch < 1 ? 1 : rch, A, lda, Bm, ldb, sc, scratch);
-  k_tr_wgrad_sum<<<blocks((size_t)dout * dinb), TB, 0, st>>>(nz, dout, din, dinb, scratch, G + wofs,
-                                                            bofs ? G + *bofs : nullptr);
+  const bool direct = nz == 1;
+  k_tr_wgrad<<<dim3((unsigned)((dinb + TG_T - 1) / TG_T), (unsigned)((dout + TG_T - 1) / TG_T),
+                    (unsigned)(hd.n > 1 ? hd.n : nz)),
+               256, 0, st>>>(rows, range, dout, din, dinb, rch < 1 ? 1 : rch, hd.n > 1 ? hd.stride : 0, A, lda, Bm,
+                             ldb, sc, direct ? nullptr : scratch, G + wofs, bofs ? G + *bofs : nullptr);
+  if (!direct)
+    k_tr_wgrad_sum<<<blocks((size_t)dout * dinb), TB, 0, st>>>(nz, dout, din, dinb, scratch, G + wofs,
+                                                              bofs ? G + *bofs : nullptr);
 }
 
 // One pass.  Real (S = double): E, F into w.E, w.Fo.  Tangent (S = Dual, with
@@ -958,16 +1093,20 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     y = (const S*)w.shy[m];
     dy = hp.shared_dims[m];
   }
-  if (REAL) k_tr_group<<<1, 64, 0, st>>>(B, H, g->struct_ptr, dataset_id, w.perm, w.hstart, w.bad);
+  if (REAL) k_tr_group<<<1, 256, 0, st>>>(B, N, H, g->struct_ptr, g->atom_struct, dataset_id, w.perm, w.hstart,
+                                          w.bad, (int32_t*)w.c);   // c is written by the loss, later
   const int32_t* slots = w.hstart + H;
   k_tr_gather<S><<<blocks((size_t)N * dy), TB, 0, st>>>(N, dy, slots, w.perm, y, (S*)w.yg);
-  for (int h = 0; h < H; ++h) {
+  Heads heads;
+  heads.n = H;
+  heads.stride = H > 1 ? (long long)(L.branch_w[1][0] - L.branch_w[0][0]) : 0;
+  {
     const S* x = (const S*)w.yg;
     int dx = dy;
     for (int m = 0; m < nb; ++m) {
       const int d = hp.branch_dims[m];
-      dense<S>(st, th, N, w.hstart + h, dx, d, x, dx, L.branch_w[h][m], &L.branch_b[h][m], m + 1 < nb,
-               (S*)w.brz[m], (S*)w.bry[m], d);
+      dense<S>(st, th, N, w.hstart, dx, d, x, dx, L.branch_w[0][m], &L.branch_b[0][m], m + 1 < nb, (S*)w.brz[m],
+               (S*)w.bry[m], d, heads);
       x = (const S*)w.bry[m];
       dx = d;
     }
@@ -986,10 +1125,10 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
   for (int m = nb - 1; m >= 0; --m) {
     const int dout = hp.branch_dims[m], din = m > 0 ? hp.branch_dims[m - 1] : dy;
     const S* xin = m > 0 ? (const S*)w.bry[m - 1] : (const S*)w.yg;
-    for (int h = 0; h < H; ++h) {
-      if (!REAL) wgrad<S>(st, G, w.wsum, N, w.hstart + h, dout, din, gcur, dout, xin, din, L.branch_w[h][m], &L.branch_b[h][m]);
-      dense_t<S>(st, th, N, w.hstart + h, dout, din, gcur, dout, L.branch_w[h][m], gnext, din);
-    }
+    if constexpr (!REAL)
+      wgrad(st, G, w.wsum, N, w.hstart, dout, din, gcur, dout, xin, din, L.branch_w[0][m], &L.branch_b[0][m], nullptr,
+            heads);
+    dense_t<S>(st, th, N, w.hstart, dout, din, gcur, dout, L.branch_w[0][m], gnext, din, (const S*)nullptr, 0, heads);
     if (m > 0)
       k_tr_mul_dsilu<S><<<blocks((size_t)N * din), TB, 0, st>>>(N, nullptr, din, gnext, din, (const S*)w.brz[m - 1],
                                                                  din);
@@ -1009,7 +1148,7 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     const int dout = hp.shared_dims[m], din = m > 0 ? hp.shared_dims[m - 1] : F;
     const S* xin = m > 0 ? (const S*)w.shy[m - 1] : (const S*)w.sL;
     k_tr_mul_dsilu<S><<<blocks((size_t)N * dout), TB, 0, st>>>(N, nullptr, dout, gcur, dout, (const S*)w.shz[m], dout);
-    if (!REAL) wgrad<S>(st, G, w.wsum, N, nullptr, dout, din, gcur, dout, xin, din, L.shared_w[m], &L.shared_b[m]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, dout, din, gcur, dout, xin, din, L.shared_w[m], &L.shared_b[m]);
     dense_t<S>(st, th, N, nullptr, dout, din, gcur, dout, L.shared_w[m], gnext, din);
     S* t = gcur;
     gcur = gnext;
@@ -1031,16 +1170,16 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     // update block: (gs, gv) at s', v' -> (gs2, gv2) at s_mid, v_mid
     k_tr_upd_bwd1<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, F, gs, gv, (S*)w.U[l], (S*)w.V[l], (S*)w.a[l],
                                                            (S*)w.ga, (S*)w.gU, (S*)w.gV);
-    if (!REAL) wgrad<S>(st, G, w.wsum, N, nullptr, F3, F, (S*)w.ga, F3, (S*)w.aa[l], F, a[A_UPD_W2], &a[A_UPD_B2]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F3, F, (S*)w.ga, F3, (S*)w.aa[l], F, a[A_UPD_W2], &a[A_UPD_B2]);
     dense_t<S>(st, th, N, nullptr, F3, F, (S*)w.ga, F3, a[A_UPD_W2], (S*)w.gaa, F);
     k_tr_mul_dsilu<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, nullptr, F, (S*)w.gaa, F, (S*)w.za[l], F);
-    if (!REAL) wgrad<S>(st, G, w.wsum, N, nullptr, F, 2 * F, (S*)w.gaa, F, (S*)w.xin[l], 2 * F, a[A_UPD_W1], &a[A_UPD_B1]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F, 2 * F, (S*)w.gaa, F, (S*)w.xin[l], 2 * F, a[A_UPD_W1], &a[A_UPD_B1]);
     dense_t<S>(st, th, N, nullptr, F, 2 * F, (S*)w.gaa, F, a[A_UPD_W1], (S*)w.gin, 2 * F);
     k_tr_upd_bwd2<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, F, (S*)w.gin, (S*)w.xin[l], (S*)w.V[l], gs,
                                                            (S*)w.gV, gs2);
-    if (!REAL) {
-      wgrad<S>(st, G, w.wsum, 3 * N, nullptr, F, F, (S*)w.gU, F, (S*)w.vmid[l], F, a[A_U], nullptr);
-      wgrad<S>(st, G, w.wsum, 3 * N, nullptr, F, F, (S*)w.gV, F, (S*)w.vmid[l], F, a[A_V], nullptr);
+    if constexpr (!REAL) {
+      wgrad(st, G, w.wsum, 3 * N, nullptr, F, F, (S*)w.gU, F, (S*)w.vmid[l], F, a[A_U], nullptr);
+      wgrad(st, G, w.wsum, 3 * N, nullptr, F, F, (S*)w.gV, F, (S*)w.vmid[l], F, a[A_V], nullptr);
     }
     dense_t<S>(st, th, 3 * N, nullptr, F, F, (S*)w.gU, F, a[A_U], gv2, F, gv, F);
     dense_t<S>(st, th, 3 * N, nullptr, F, F, (S*)w.gV, F, a[A_V], gv2, F, gv2, F);
@@ -1049,28 +1188,27 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
                                                               (S*)w.v[l], (S*)w.lin[l], (S*)w.fc, (S*)w.rhat, gs2,
                                                               gv2, (S*)w.gh, gv, (S*)w.gw);
     if (E > 0) {
-      if (REAL) {
+      if constexpr (REAL) {
         // lin' = W_f g'(d) for dE/dd
-        k_tr_dense<double, false><<<dgrid((int)E, F3), 256, 0, st>>>((int)E, nullptr, K, F3, w.dbasis, K,
-                                                                     th + a[A_FILT_W], K, 1, nullptr, nullptr, 0,
-                                                                     nullptr, w.linp, F3);
+        dense<double>(st, th, (int)E, nullptr, K, F3, w.dbasis, K, a[A_FILT_W], nullptr, false, nullptr, w.linp, F3);
         k_tr_edge_bwd<<<(unsigned)((E + 3) / 4), 256, 0, st>>>(E, F, g->recv, g->col, (const double*)w.h[l],
                                                                (const double*)w.lin[l], w.linp, (const double*)w.fc,
                                                                w.dfc, (const double*)gv2, (const double*)w.gw, w.gd,
                                                                w.grh);
       } else {
-        wgrad<S>(st, G, w.wsum, (int)E, nullptr, F3, K, (S*)w.gw, F3, (S*)w.basis, K, a[A_FILT_W], &a[A_FILT_B], (S*)w.fc);
+        wgrad(st, G, w.wsum, (int)E, nullptr, F3, K, (S*)w.gw, F3, (S*)w.basis, K, a[A_FILT_W], &a[A_FILT_B], (S*)w.fc);
       }
     }
     // phi: dE/dh -> dE/ds before the message (its residual gs2 added)
-    if (!REAL) wgrad<S>(st, G, w.wsum, N, nullptr, F3, F, (S*)w.gh, F3, (S*)w.a1[l], F, a[A_PHI_W2], &a[A_PHI_B2]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F3, F, (S*)w.gh, F3, (S*)w.a1[l], F, a[A_PHI_W2], &a[A_PHI_B2]);
     dense_t<S>(st, th, N, nullptr, F3, F, (S*)w.gh, F3, a[A_PHI_W2], (S*)w.ga1, F);
     k_tr_mul_dsilu<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, nullptr, F, (S*)w.ga1, F, (S*)w.z1[l], F);
-    if (!REAL) wgrad<S>(st, G, w.wsum, N, nullptr, F, F, (S*)w.ga1, F, (S*)w.s[l], F, a[A_PHI_W1], &a[A_PHI_B1]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F, F, (S*)w.ga1, F, (S*)w.s[l], F, a[A_PHI_W1], &a[A_PHI_B1]);
     dense_t<S>(st, th, N, nullptr, F, F, (S*)w.ga1, F, a[A_PHI_W1], gs, F, gs2, F);
   }
   if (!REAL)
-    k_tr_emb_grad<S><<<blocks((size_t)hp.n_species * F), TB, 0, st>>>(N, F, hp.n_species, g->species, gs, G + L.emb);
+    k_tr_emb_grad<S><<<dim3((unsigned)hp.n_species, (unsigned)((F + 255) / 256)), 256, 0, st>>>(N, F, g->species, gs,
+                                                                                               G + L.emb);
   if (REAL) {
     if (E > 0)
       k_tr_edge_dr<<<blocks((size_t)E), TB, 0, st>>>(E, w.dist, (const double*)w.rhat, w.gd, w.grh, w.gr);
