@@ -529,7 +529,7 @@ __global__ void __launch_bounds__(256) k_blend_grad(int N, int H, int F, A skip,
 // The per-atom scratch holds g_n.
 // Waves per workgroup of the reverse update and phi kernels: 4, or more
 // where the LDS tile leaves room for only one workgroup per CU (measured:
-// 16 for FP32; 8 for FP64, whose 3F-wide operands then sit in global memory).
+// 16 for FP32, 8 for FP64).
 template <class P, int F>
 constexpr int ub_nw() {
   return (size_t)16 * (4 * F + 2 * P::PAD) * sizeof(typename P::T) > 64 * 1024
@@ -548,22 +548,18 @@ struct UpdBwdArgs {
   void* gv_out;
   void* scratch;
   int sw;
-  void* xbuf;        // GX: per-workgroup [16][3F + PAD] buffers in global memory
   DenseDev uvT, upd1T, upd2T;
 };
 
-// GX: the 3F-wide operand buffer R1 lives in global memory (a region per
-// workgroup; the MFMA operand reads go through the caches) when 16 rows of
-// 4F do not fit the LDS (FP64 at F = 384).
-template <class P, int F, bool GX>
+template <class P, int F>
 __global__ void __launch_bounds__((64 * ub_nw<P, F>())) k_update_bwd(UpdBwdArgs a) {
   using T = typename P::T;
   using A = typename P::A;
   using C = typename P::C;
   constexpr int TM = 16, LD1 = 3 * F + P::PAD, LD2 = F + P::PAD;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  T* R1 = GX ? (T*)a.xbuf + (size_t)blockIdx.x * TM * LD1 : (T*)smem;
-  T* R2 = GX ? (T*)smem : R1 + TM * LD1;
+  T* R1 = (T*)smem;
+  T* R2 = R1 + TM * LD1;
   const int lane = threadIdx.x & 63;
   const size_t row0 = (size_t)blockIdx.x * TM;
   const int N = a.N;
@@ -779,21 +775,18 @@ struct PhiBwdArgs {
   const void* gh;      // [N][3F]
   const void* gs_mid;  // [N][F]
   void* gs_out;
-  void* scratch;       // per-atom rows of sw elements (FP64 at F = 384 only)
-  int sw;
-  void* xbuf;          // GX: as for the update
   DenseDev phi1, phi1T, phi2T;
 };
 
-template <class P, int F, bool GX>
+template <class P, int F>
 __global__ void __launch_bounds__((64 * ub_nw<P, F>())) k_phi_bwd(PhiBwdArgs a) {
   using T = typename P::T;
   using A = typename P::A;
   using C = typename P::C;
   constexpr int TM = 16, LD1 = 3 * F + P::PAD, LD2 = F + P::PAD;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  T* R1 = GX ? (T*)a.xbuf + (size_t)blockIdx.x * TM * LD1 : (T*)smem;
-  T* R2 = GX ? (T*)smem : R1 + TM * LD1;
+  T* R1 = (T*)smem;
+  T* R2 = R1 + TM * LD1;
   const int lane = threadIdx.x & 63;
   const size_t row0 = (size_t)blockIdx.x * TM;
   const int N = a.N;
@@ -802,25 +795,16 @@ __global__ void __launch_bounds__((64 * ub_nw<P, F>())) k_phi_bwd(PhiBwdArgs a) 
   __syncthreads();
   // silu'(W1 s + b1) stays in the registers of the lane that formed it (both
   // F-wide layers hand feature tile ct to wave ct % NW, call ct / NW of it)
-  // where a wave has at most two tiles; otherwise (FP64 at F = 384) it goes
-  // through the per-atom scratch rows.
   constexpr int NW = ub_nw<P, F>(), TPW = (F / 16 + NW - 1) / NW;
-  constexpr bool REG = TPW <= 2;
-  A* scr = (A*)a.scratch;
-  A ds[REG ? TPW : 1][4];
+  A ds[TPW][4];
   dense_tiles<P, 1, NW, F>(R2, LD2, a.phi1, [&](int ct, C* acc) {
     const int col = ct * 16 + (lane & 15), k = ct / NW;
     const A bias = ((const A*)a.phi1.b)[col];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const A d = dsilu<A>(acc[0][i] + bias);
-      if constexpr (REG) {
 #pragma unroll
-        for (int j = 0; j < TPW; ++j) ds[j][i] = j == k ? d : ds[j][i];
-      } else {
-        const int r = P::row(lane, i);
-        if (row0 + r < (size_t)N) scr[(row0 + r) * a.sw + col] = d;
-      }
+      for (int j = 0; j < TPW; ++j) ds[j][i] = j == k ? d : ds[j][i];
     }
   });
   __syncthreads();
@@ -829,16 +813,10 @@ __global__ void __launch_bounds__((64 * ub_nw<P, F>())) k_phi_bwd(PhiBwdArgs a) 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = P::row(lane, i);
-      A g = 0;
-      if constexpr (REG) {
-        A d = ds[0][i];
+      A d = ds[0][i];
 #pragma unroll
-        for (int j = 1; j < TPW; ++j) d = j == k ? ds[j][i] : d;
-        g = acc[0][i] * d;
-      } else {
-        if (row0 + r < (size_t)N) g = acc[0][i] * scr[(row0 + r) * a.sw + col];
-      }
-      R2[r * LD2 + col] = P::st(row0 + r < (size_t)N ? g : A(0));
+      for (int j = 1; j < TPW; ++j) d = j == k ? ds[j][i] : d;
+      R2[r * LD2 + col] = P::st(row0 + r < (size_t)N ? acc[0][i] * d : A(0));
     }
   });
   __syncthreads();
@@ -851,6 +829,253 @@ __global__ void __launch_bounds__((64 * ub_nw<P, F>())) k_phi_bwd(PhiBwdArgs a) 
       if (g < (size_t)N) go[g * F + col] = gm[g * F + col] + acc[0][i];
     }
   });
+}
+
+// ------------------------------------ update and phi, back, in chunks of F ----
+// The same products with the operands in F-wide chunks of their contraction
+// (the 3F-wide g_a, the 2F-wide [g_U ; g_V]) that alternate between two LDS
+// buffers while the accumulators stay in registers: a chunk is filled, one
+// barrier, multiplied; the next fill writes the other buffer, so a wave that
+// is done early fills while the others multiply.  FP64 at F = 384 fits the
+// LDS this way (148 KiB instead of 16 rows of 4F = 198 KiB, whose 3F-wide
+// part had to be read from global memory by every wave), and a wave's feature
+// tiles share each activation read.
+//
+// acc[t] += X [16][F] W^T for the wave's feature tiles ct0 + wave + NW t,
+// contraction k-blocks [kb0, kb0 + F / KC) of a layer of nkb k-blocks.
+template <class P, int F, int NW, int TPW>
+__device__ __forceinline__ void chunk_mma(const typename P::T* X, int ldx, const DenseDev& L, int ct0, int kb0,
+                                          typename P::C* acc) {
+  using D = dense_t<P>;
+  using T = typename P::T;
+  using Fr = typename D::Fr;
+  constexpr int NKB = F / D::KC;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nkb = L.din_p / D::KC;
+  const T* wp[TPW];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+    wp[t] = (const T*)L.w + (((size_t)(ct0 + wave + NW * t) * nkb + kb0) * 64 + lane) * D::KPL;
+  kloop<D, NKB, ring_depth<D, TPW, 2>(), TPW, 1>(
+      X + (size_t)(lane & 15) * ldx + (lane >> 4) * D::KPL, ldx,
+      [&](int kb, Fr* f) {
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) f[t] = D::frag(wp[t] + (size_t)kb * 64 * D::KPL);
+      },
+      [&](int kb, const Fr* x, const Fr* f) {
+#pragma unroll
+        for (int j = 0; j < D::SUB; ++j)
+#pragma unroll
+          for (int t = 0; t < TPW; ++t) acc[t] = D::mfma_sub(x[0], f[t], acc[t], j);
+      });
+}
+
+// FP64 takes this form from F = 256 on, where 16 rows of 4F leave one
+// workgroup per CU or none: update per launch, before and after, F = 384
+// (15,762 atoms) 2,532 -> 1,129 us, F = 256 (14,075 atoms) 624 -> 574; phi 922
+// -> 478 and 258 -> 216.  Below, and in FP32, two workgroups fit and the
+// whole-row form is the faster one (F = 128 FP64 forces 0.5 % slower in
+// chunks, F = 64 2 %; FP32 update 5 to 15 % slower).
+template <class P, int F>
+constexpr bool chunked() { return P::PREC == PAINN_FP64 && F >= 256; }
+// Waves of a chunked workgroup.
+template <class P, int F>
+constexpr int uc_nw() {
+  return F == 384 ? 12 : F >= 128 ? 8 : 4;
+}
+
+template <class P, int F>
+__global__ void __launch_bounds__((64 * uc_nw<P, F>())) k_update_bwd_chunk(UpdBwdArgs a) {
+  using T = typename P::T;
+  using A = typename P::A;
+  using C = typename P::C;
+  static_assert(std::is_same<T, A>::value, "FP64 / FP32");
+  constexpr int NW = uc_nw<P, F>(), NT = 64 * NW, TM = 16, LD = F + P::PAD, TPW = F / 16 / NW;
+  static_assert(F / 16 % NW == 0, "whole feature tiles per wave");
+  constexpr int V = 2, EV = TM * F / V;          // elements in pairs
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  T* X[2] = {(T*)smem, (T*)smem + TM * LD};
+  A* GN = (A*)smem + 2 * TM * LD;                // dE/d|V|, then that over |V|
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const size_t row0 = (size_t)blockIdx.x * TM;
+  const int N = a.N;
+  const A* uv = (const A*)a.uv;
+  const A* zs = (const A*)a.z;
+  const A* ag = (const A*)a.ag;
+  const A* gs = (const A*)a.gs;
+  const A* gv = (const A*)a.gv;
+  struct alignas(V * sizeof(A)) Pr { A x[V]; };
+  auto ld = [](const A* p) { return *(const Pr*)p; };
+  // fill a chunk: fn(row, feature, the pair)
+  auto fill = [&](T* dst, auto&& fn) {
+#pragma unroll
+    for (int x = threadIdx.x; x < EV; x += NT) {
+      const int r = x / (F / V), f = (x % (F / V)) * V;
+      Pr o;
+      for (int k = 0; k < V; ++k) o.x[k] = A(0);
+      if (row0 + r < (size_t)N) o = fn(row0 + r, r, f);
+      for (int k = 0; k < V; ++k) dst[r * LD + f + k] = o.x[k];
+    }
+  };
+  C acc[TPW], acc2[TPW];
+  auto zero = [&](C* c) {
+    for (int t = 0; t < TPW; ++t)
+      for (int i = 0; i < 4; ++i) c[t][i] = 0;
+  };
+  // g_z = (W2a^T g_a) * silu'(z), g_a = [sum_c g_v U | g_s <U, V> | g_s]
+  zero(acc);
+  fill(X[0], [&](size_t i, int, int f) {
+    Pr o;
+    for (int k = 0; k < V; ++k) o.x[k] = 0;
+    for (int c = 0; c < 3; ++c) {
+      const Pr u = ld(uv + (i * 3 + c) * 2 * F + f), g = ld(gv + i * 3 * F + c * F + f);
+      for (int k = 0; k < V; ++k) o.x[k] += g.x[k] * u.x[k];
+    }
+    return o;
+  });
+  __syncthreads();
+  chunk_mma<P, F, NW, TPW>(X[0], LD, a.upd2T, 0, 0, acc);
+  fill(X[1], [&](size_t i, int, int f) {
+    Pr o;
+    for (int k = 0; k < V; ++k) o.x[k] = 0;
+    for (int c = 0; c < 3; ++c) {
+      const Pr u = ld(uv + (i * 3 + c) * 2 * F + f), w = ld(uv + (i * 3 + c) * 2 * F + F + f);
+      for (int k = 0; k < V; ++k) o.x[k] += u.x[k] * w.x[k];
+    }
+    const Pr g = ld(gs + i * F + f);
+    for (int k = 0; k < V; ++k) o.x[k] *= g.x[k];
+    return o;
+  });
+  __syncthreads();
+  chunk_mma<P, F, NW, TPW>(X[1], LD, a.upd2T, 0, F / dense_t<P>::KC, acc);
+  fill(X[0], [&](size_t i, int, int f) { return ld(gs + i * F + f); });
+  __syncthreads();
+  chunk_mma<P, F, NW, TPW>(X[0], LD, a.upd2T, 0, 2 * F / dense_t<P>::KC, acc);
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int col = (wave + NW * t) * 16 + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = P::row(lane, i);
+      A g = 0;
+      if (row0 + r < (size_t)N) g = acc[t][i] * dsilu<A>(zs[(row0 + r) * F + col]);
+      X[1][r * LD + col] = g;
+    }
+  }
+  __syncthreads();
+  // [g_s' ; g_n] = W1a^T g_z
+  zero(acc);
+  zero(acc2);
+  chunk_mma<P, F, NW, TPW>(X[1], LD, a.upd1T, 0, 0, acc);
+  chunk_mma<P, F, NW, TPW>(X[1], LD, a.upd1T, F / 16, 0, acc2);
+  A* gs_out = (A*)a.gs_out;
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int col = (wave + NW * t) * 16 + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = P::row(lane, i);
+      const size_t g = row0 + r;
+      GN[r * LD + col] = acc2[t][i];
+      if (g < (size_t)N) gs_out[g * F + col] = gs[g * F + col] + acc[t][i];
+    }
+  }
+  __syncthreads();
+  // per component: g_v + U^T g_U + V^T g_V
+  A* gv_out = (A*)a.gv_out;
+  for (int c = 0; c < 3; ++c) {
+    zero(acc);
+    fill(X[0], [&](size_t i, int, int f) {
+      const Pr w = ld(uv + (i * 3 + c) * 2 * F + F + f), g = ld(gv + i * 3 * F + c * F + f);
+      const Pr avv = ld(ag + i * 2 * F + f), asv = ld(ag + i * 2 * F + F + f), s = ld(gs + i * F + f);
+      Pr o;
+      for (int k = 0; k < V; ++k) o.x[k] = g.x[k] * avv.x[k] + s.x[k] * asv.x[k] * w.x[k];
+      return o;
+    });
+    __syncthreads();
+    chunk_mma<P, F, NW, TPW>(X[0], LD, a.uvT, 0, 0, acc);
+    fill(X[1], [&](size_t i, int r, int f) {
+      const Pr u = ld(uv + (i * 3 + c) * 2 * F + f), w = ld(uv + (i * 3 + c) * 2 * F + F + f);
+      const Pr asv = ld(ag + i * 2 * F + F + f), s = ld(gs + i * F + f);
+      A* gn = GN + r * LD + f;
+      if (c == 0) {
+        // the norm's factor dE/d|V| / |V| (0 where V = 0), once
+        const Pr v0 = w, v1 = ld(uv + (i * 3 + 1) * 2 * F + F + f), v2 = ld(uv + (i * 3 + 2) * 2 * F + F + f);
+        for (int k = 0; k < V; ++k) {
+          const A nv = sqrt(v0.x[k] * v0.x[k] + v1.x[k] * v1.x[k] + v2.x[k] * v2.x[k]);
+          gn[k] = nv > A(0) ? gn[k] / nv : A(0);
+        }
+      }
+      Pr o;
+      for (int k = 0; k < V; ++k) o.x[k] = s.x[k] * asv.x[k] * u.x[k] + gn[k] * w.x[k];
+      return o;
+    });
+    __syncthreads();
+    chunk_mma<P, F, NW, TPW>(X[1], LD, a.uvT, 0, F / dense_t<P>::KC, acc);
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      const int col = (wave + NW * t) * 16 + (lane & 15);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const size_t g = row0 + P::row(lane, i);
+        if (g < (size_t)N) {
+          const size_t o = g * 3 * F + c * F + col;
+          gv_out[o] = gv[o] + acc[t][i];
+        }
+      }
+    }
+  }
+}
+
+template <class P, int F>
+__global__ void __launch_bounds__((64 * uc_nw<P, F>())) k_phi_bwd_chunk(PhiBwdArgs a) {
+  using T = typename P::T;
+  using A = typename P::A;
+  using C = typename P::C;
+  static_assert(std::is_same<T, A>::value, "FP64 / FP32");
+  constexpr int NW = uc_nw<P, F>(), TM = 16, LD = F + P::PAD, TPW = F / 16 / NW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  T* X[2] = {(T*)smem, (T*)smem + TM * LD};
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const size_t row0 = (size_t)blockIdx.x * TM;
+  const int N = a.N;
+  C z[TPW], acc[TPW];
+  for (int t = 0; t < TPW; ++t)
+    for (int i = 0; i < 4; ++i) z[t][i] = acc[t][i] = 0;
+  stage_rows<P, F, TM>(X[0], LD, (const T*)a.s, F, row0, N);
+  __syncthreads();
+  chunk_mma<P, F, NW, TPW>(X[0], LD, a.phi1, 0, 0, z);
+  const A* gh = (const A*)a.gh;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    stage_rows<P, F, TM>(X[(k + 1) & 1], LD, gh + k * F, 3 * F, row0, N);
+    __syncthreads();
+    chunk_mma<P, F, NW, TPW>(X[(k + 1) & 1], LD, a.phi2T, 0, k * F / dense_t<P>::KC, acc);
+  }
+  // (X[0] was last read before the last barrier)
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int col = (wave + NW * t) * 16 + (lane & 15);
+    const A bias = ((const A*)a.phi1.b)[col];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = P::row(lane, i);
+      X[0][r * LD + col] = row0 + r < (size_t)N ? acc[t][i] * dsilu<A>(z[t][i] + bias) : A(0);
+      acc[t][i] = 0;
+    }
+  }
+  __syncthreads();
+  chunk_mma<P, F, NW, TPW>(X[0], LD, a.phi1T, 0, 0, acc);
+  const A* gm = (const A*)a.gs_mid;
+  A* go = (A*)a.gs_out;
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int col = (wave + NW * t) * 16 + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t g = row0 + P::row(lane, i);
+      if (g < (size_t)N) go[g * F + col] = gm[g * F + col] + acc[t][i];
+    }
+  }
 }
 
 // ---------------------------------------------------------- message, back ----
@@ -1729,12 +1954,18 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
   const int kcols = pm->layers[0].filt_mma.din_p;
   const int NW = message_bwd_slots<P, F>(kcols / P::KC);   // per-edge slots (waves of the message kernel)
   if (N == 0) return hipSuccess;
-  // LDS of the tile kernels: 16 rows of 3F + F (+ padding), or of F alone
-  // with the 3F-wide buffer in global memory
-  constexpr bool UGX = (size_t)16 * (4 * F + 2 * P::PAD) * sizeof(T) > 160 * 1024;
-  const size_t smem_ub = (size_t)16 * ((UGX ? 0 : 3 * F + P::PAD) + F + P::PAD) * sizeof(T);
-  hipError_t e = allow_lds(k_update_bwd<P, F, UGX>, smem_ub);
-  if (e == hipSuccess) e = allow_lds(k_phi_bwd<P, F, UGX>, smem_ub);
+  // LDS of the tile kernels: 16 rows of 3F + F (+ padding), or chunks of F
+  const size_t smem_ub = (size_t)16 * (4 * F + 2 * P::PAD) * sizeof(T);
+  constexpr bool CHUNK = chunked<P, F>();
+  const size_t smem_pc = (size_t)2 * 16 * (F + P::PAD) * sizeof(T), smem_uc = smem_pc / 2 * 3;
+  hipError_t e;
+  if constexpr (CHUNK) {
+    e = allow_lds(k_update_bwd_chunk<P, F>, smem_uc);
+    if (e == hipSuccess) e = allow_lds(k_phi_bwd_chunk<P, F>, smem_pc);
+  } else {
+    e = allow_lds(k_update_bwd<P, F>, smem_ub);
+    if (e == hipSuccess) e = allow_lds(k_phi_bwd<P, F>, smem_ub);
+  }
   if (e != hipSuccess) return e;
   if (E > 0) {
     const double delta = hp.cutoff / (hp.K - 1);
@@ -1844,10 +2075,9 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
     ua.uvT = Ld.uvT;
     ua.upd1T = Ld.upd1T;
     ua.upd2T = Ld.upd2T;
-    ua.xbuf = ba.xbuf;
-    if (UGX && (size_t)tiles * 16 * (3 * F + P::PAD) * sizeof(T) > ba.xbuf_bytes) return hipErrorInvalidValue;
     prof_mark(ba.prof, st, KC_BWD_UPDATE, true);
-    k_update_bwd<P, F, UGX><<<tiles, 64 * ub_nw<P, F>(), smem_ub, st>>>(ua);
+    if constexpr (CHUNK) k_update_bwd_chunk<P, F><<<tiles, 64 * uc_nw<P, F>(), smem_uc, st>>>(ua);
+    else k_update_bwd<P, F><<<tiles, 64 * ub_nw<P, F>(), smem_ub, st>>>(ua);
     prof_mark(ba.prof, st, KC_BWD_UPDATE, false);
     MsgBwdArgs ma;
     ma.N = N;
@@ -1878,14 +2108,12 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
       pa.gh = ba.gh;
       pa.gs_mid = ba.gs2;
       pa.gs_out = ba.gs;
-      pa.scratch = ba.scratch;
-      pa.sw = ba.scratch_w;
       pa.phi1 = Ld.phi1;
       pa.phi1T = Ld.phi1T;
       pa.phi2T = Ld.phi2T;
-      pa.xbuf = ba.xbuf;
       prof_mark(ba.prof, st, KC_BWD_PHI, true);
-      k_phi_bwd<P, F, UGX><<<tiles, 64 * ub_nw<P, F>(), smem_ub, st>>>(pa);
+      if constexpr (CHUNK) k_phi_bwd_chunk<P, F><<<tiles, 64 * uc_nw<P, F>(), smem_pc, st>>>(pa);
+      else k_phi_bwd<P, F><<<tiles, 64 * ub_nw<P, F>(), smem_ub, st>>>(pa);
       prof_mark(ba.prof, st, KC_BWD_PHI, false);
     }
   }

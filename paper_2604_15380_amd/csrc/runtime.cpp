@@ -950,28 +950,21 @@ static int forces_scratch_width(const Hyper& hp) {
   return zw > hp.F ? zw : hp.F;
 }
 
-// Operand buffers in global memory, for reverse tile kernels whose 16-row
-// tiles do not fit the LDS: [16][3F + pad] per update / phi tile (FP64 at
-// F = 384), [2][16][widest head layer + 2] per heads workgroup.
+// Operand buffers in global memory, where the reverse heads kernel's 16-row
+// tiles do not fit the LDS (layers wider than ~580 in FP64): [2][16][widest
+// layer + padding] per workgroup.
 static size_t forces_xbuf_bytes(int prec, const Hyper& hp, int N, bool blend) {
-  const size_t eb = elem_bytes(prec), F = hp.F, tiles = ((size_t)N + 15) / 16;
+  const size_t eb = elem_bytes(prec);
   const bool wide = branch_wide(hp);
   const size_t head_tiles = ((size_t)N * (blend && !wide ? hp.n_heads : 1) + 15) / 16;
-  // LDS row padding of the dense kernels' activation tiles (elements)
-  const size_t pad = lds_pad(prec);
-  size_t x = 0;
-  if (16 * (4 * F + 2 * pad) * eb > 160 * 1024) x = tiles * 16 * (3 * F + pad) * eb;
   int wmax = hp.F;
   for (int d : hp.shared_dims) wmax = wmax > pad32(d) ? wmax : pad32(d);
   for (size_t mm = 0; mm + 1 < hp.branch_dims.size() && !wide; ++mm)
     wmax = wmax > pad32(hp.branch_dims[mm]) ? wmax : pad32(hp.branch_dims[mm]);
-  const size_t hb = (size_t)2 * 16 * (wmax + pad) * eb;
-  if (hb > 150 * 1024) {
-    const size_t grid = head_tiles + hp.n_heads < (size_t)HB_GRID ? head_tiles + hp.n_heads : (size_t)HB_GRID;
-    const size_t h = grid * hb;
-    x = x > h ? x : h;
-  }
-  return x;
+  const size_t hb = (size_t)2 * 16 * (wmax + lds_pad(prec)) * eb;
+  if (hb <= 150 * 1024) return 0;
+  const size_t grid = head_tiles + hp.n_heads < (size_t)HB_GRID ? head_tiles + hp.n_heads : (size_t)HB_GRID;
+  return grid * hb;
 }
 
 // per-atom rows, or the reverse heads kernel's 16 rows per workgroup
