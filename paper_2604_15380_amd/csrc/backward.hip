@@ -21,6 +21,7 @@
 // constant in the positions).  Where |V v| = 0 the norm's gradient is taken
 // as zero.
 #include "mfma.h"
+#include "rows.h"
 
 namespace {
 
@@ -2076,7 +2077,30 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
     ua.upd1T = Ld.upd1T;
     ua.upd2T = Ld.upd2T;
     prof_mark(ba.prof, st, KC_BWD_UPDATE, true);
-    if constexpr (CHUNK) k_update_bwd_chunk<P, F><<<tiles, 64 * uc_nw<P, F>(), smem_uc, st>>>(ua);
+    // small batches: one launch per dense layer (g_z goes through the space of
+    // g_h, which the message writes next; g_n and phi's g through the scratch)
+    const bool small = rows::small_rows<P, F>(N, true);
+    rows::Args ra{};
+    if (small) {
+      ra.N = N;
+      ra.uv = ua.uv;
+      ra.z = ua.z;
+      ra.ag = ua.ag;
+      ra.gs = ua.gs;
+      ra.gv = ua.gv;
+      ra.gs_out = ua.gs_out;
+      ra.gv_out = ua.gv_out;
+      ra.gn = ba.scratch;
+      ra.sw = ba.scratch_w;
+      ra.t = ba.gh;
+      ra.ts = F;
+      ra.d0 = ua.upd2T;
+      rows::launch<P, F, rows::B_GATE2>(st, ra);
+      ra.d0 = ua.upd1T;
+      rows::launch<P, F, rows::B_GATE1>(st, ra);
+      ra.d0 = ua.uvT;
+      rows::launch<P, F, rows::B_UV>(st, ra);
+    } else if constexpr (CHUNK) k_update_bwd_chunk<P, F><<<tiles, 64 * uc_nw<P, F>(), smem_uc, st>>>(ua);
     else k_update_bwd<P, F><<<tiles, 64 * ub_nw<P, F>(), smem_ub, st>>>(ua);
     prof_mark(ba.prof, st, KC_BWD_UPDATE, false);
     MsgBwdArgs ma;
@@ -2112,7 +2136,19 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
       pa.phi1T = Ld.phi1T;
       pa.phi2T = Ld.phi2T;
       prof_mark(ba.prof, st, KC_BWD_PHI, true);
-      if constexpr (CHUNK) k_phi_bwd_chunk<P, F><<<tiles, 64 * uc_nw<P, F>(), smem_pc, st>>>(pa);
+      if (small) {
+        ra.s = pa.s;
+        ra.gh = pa.gh;
+        ra.gm = pa.gs_mid;
+        ra.gs_out = pa.gs_out;
+        ra.t = ba.scratch;
+        ra.ts = ba.scratch_w;
+        ra.d0 = pa.phi1;
+        ra.d1 = pa.phi2T;
+        rows::launch<P, F, rows::B_PHI2>(st, ra);
+        ra.d0 = pa.phi1T;
+        rows::launch<P, F, rows::B_PHI1>(st, ra);
+      } else if constexpr (CHUNK) k_phi_bwd_chunk<P, F><<<tiles, 64 * uc_nw<P, F>(), smem_pc, st>>>(pa);
       else k_phi_bwd<P, F><<<tiles, 64 * ub_nw<P, F>(), smem_ub, st>>>(pa);
       prof_mark(ba.prof, st, KC_BWD_PHI, false);
     }

@@ -12,6 +12,7 @@
 
 #include "branchgemm.h"
 #include "mfma.h"
+#include "rows.h"
 
 namespace {
 
@@ -2130,6 +2131,45 @@ hipError_t forward_impl(hipStream_t st, ForwardArgs& fa) {
     if (fuse) {
       ua.phi1 = pm->layers[l + 1].phi1;
       ua.phi2 = pm->layers[l + 1].phi2;
+    }
+    if constexpr (sizeof(T) != 2) {
+      if (rows::small_rows<P, F>(N, false)) {
+        // the buffers the message has read for the last time hold what passes
+        // between the launches: the old v takes U (later phi's hidden layer),
+        // the old h takes |V|, <U, V> and the gate's hidden layer
+        const size_t nf = (size_t)N * F;
+        rows::Args ra{};
+        ra.N = N;
+        ra.s = ua.s;
+        ra.v = ua.v;
+        ra.s_out = ua.s_out;
+        ra.v_out = ua.v_out;
+        ra.h = ua.h;
+        ra.U = fa.save ? fa.v[0] : v[cur ^ 1];
+        ra.us = F;
+        ra.nrm = fa.h;
+        ra.pd = (T*)fa.h + nf;
+        ra.hid = (T*)fa.h + 2 * nf;
+        ra.save_uv = ua.save_uv;
+        ra.save_z = ua.save_z;
+        ra.save_a = ua.save_a;
+        ra.d0 = ua.uv;
+        rows::launch<P, F, rows::UV>(st, ra);
+        ra.d0 = ua.upd1;
+        rows::launch<P, F, rows::GATE1>(st, ra);
+        ra.d0 = ua.upd2;
+        rows::launch<P, F, rows::GATE2>(st, ra);
+        if (fuse) {
+          ra.s = ua.s_out;
+          ra.hid = ra.U;
+          ra.d0 = ua.phi1;
+          rows::launch<P, F, rows::PHI1>(st, ra);
+          ra.d0 = ua.phi2;
+          rows::launch<P, F, rows::PHI2>(st, ra);
+        }
+        prof_mark(fa.prof, st, KC_UPDATE, false);
+        continue;
+      }
     }
     // the saving variants exist for the reverse pass (FP64 / FP32)
     if (fa.save && sizeof(T) != 2) {
