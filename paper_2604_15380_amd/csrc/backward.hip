@@ -1127,48 +1127,64 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, size_t
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)(uint32_t)bytes, 0x00020000);
 }
 template <class V>
+__device__ __forceinline__ V buf_ld16(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff) {
+  return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+}
+template <class V>
 __device__ __forceinline__ V buf_ld8(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff) {
   return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
 }
 typedef double bwd_d2 __attribute__((ext_vector_type(2)));
 
-// Feature tiles per wave and the waves per SIMD the kernel (FP64) is
-// compiled for: one tile, two waves.
+// At 6 to 9 k-blocks a wave owns 32 channels as two feature tiles whose
+// columns interleave (column c of tile q = channel 2 c + q), so that a lane's
+// gathers of the receivers' gradients are 16-byte loads and the basis rows,
+// edge info and per-edge sums of a chunk serve twice the channels.  The
+// filter fragments of the workgroup's channels (up to 128) sit in LDS, shared
+// by two or more streams of senders.  (With one tile per wave and a filter
+// copy each: bulk reverse message 3,861 us per launch.)  With 3 k-blocks the
+// fragments fit in registers, past 9 not in the LDS: one tile per wave.
+template <int KBM>
+constexpr bool mb_pair() { return KBM <= 9; }
 template <class P, int F, int KBM>
-constexpr int mb_ftw() { return 1; }
+constexpr int mb_ftw() { return mb_pair<KBM>() ? 2 : 1; }
+// Channel groups (waves of one sender stream) and streams of a workgroup;
+// wide layers take several feature slices in consecutive workgroups.
 template <class P, int F, int KBM>
-constexpr int mb_wpe() { return 2; }
-// Waves of one feature slice (a workgroup); wide layers take several slices
-// in consecutive workgroups.
-template <class P, int F, int KBM>
-constexpr int mb_nwb() {
+constexpr int mb_ngw() {
   constexpr int nw = F / 16 / mb_ftw<P, F, KBM>();
+  if (mb_pair<KBM>()) return nw < 4 ? nw : 4;
   return nw <= 8 ? nw : (nw % 8 == 0 ? 8 : 6);
 }
+template <class P, int F, int KBM>
+constexpr int mb_ns() { return mb_pair<KBM>() ? 8 / mb_ngw<P, F, KBM>() : 1; }
+template <class P, int F, int KBM>
+constexpr int mb_nwb() { return mb_ngw<P, F, KBM>() * mb_ns<P, F, KBM>(); }
 
 // L0: the first layer, where v = 0 and only the per-edge sums are wanted
 // (as in the channel-per-lane form below): w^r, w'^s and w'^r only, no g_h,
 // g_v.
 template <class P, int F, int KBM, bool L0>
-__global__ void __launch_bounds__((64 * mb_nwb<P, F, KBM>())) __attribute__((amdgpu_waves_per_eu(mb_wpe<P, F, KBM>())))
+__global__ void __launch_bounds__((64 * mb_nwb<P, F, KBM>())) __attribute__((amdgpu_waves_per_eu(2)))
 k_message_bwd(MsgBwdArgs a) {
   using T = typename P::T;
   using A = typename P::A;
   using C = typename P::C;
   using Fr = typename P::Fr;
   constexpr int FTW = mb_ftw<P, F, KBM>(), NFT = F / 16, NW = NFT / FTW;
-  constexpr int NWB = mb_nwb<P, F, KBM>(), SLICES = NW / NWB;
-  static_assert(NW % NWB == 0, "feature slices");
+  constexpr bool PAIR = mb_pair<KBM>();
+  constexpr int NGW = mb_ngw<P, F, KBM>(), NS = mb_ns<P, F, KBM>(), NWB = NGW * NS, SLICES = NW / NGW;
+  static_assert(NW % NGW == 0, "feature slices");
   constexpr int kcols = KBM * P::KC;
   const int per_xcd = gridDim.x / 8;
   const int lb = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   const int lane = threadIdx.x & 63;
-  // With one feature tile per wave the register budget is tight (4 waves
-  // per SIMD); a wave index the compiler knows to be uniform moves address
-  // arithmetic to scalar registers.  With two tiles it has room, and the
-  // uniform form measured slower there.
-  const int wave_v = (lb % SLICES) * NWB + (threadIdx.x >> 6);
-  const int wave = FTW == 1 ? __builtin_amdgcn_readfirstlane(wave_v) : wave_v;
+  // A wave index the compiler knows to be uniform moves address arithmetic to
+  // scalar registers.
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int stream = wv / NGW;
+  const int wave = (lb % SLICES) * NGW + wv % NGW;      // channel group
+  auto chan = [&](int q, int col) { return PAIR ? 32 * wave + 2 * col + q : (FTW * wave + q) * 16 + col; };
   const T* Wf = (const T*)a.filt.w;
   const T* h = (const T*)a.h;
   const T* vv = (const T*)a.v;
@@ -1179,40 +1195,34 @@ k_message_bwd(MsgBwdArgs a) {
   const T* dbasis = (const T*)a.dbasis;
   static_assert(sizeof(A) == 8, "the MFMA form runs FP64");
   using A2 = bwd_d2;
-  // At 6 to 9 k-blocks each wave keeps its filter fragments in its own LDS
-  // region for the whole kernel (one load each at the start instead of one
-  // per chunk from L2; 13.5 KiB per wave at 9; bulk reverse message -8.5 %,
-  // molecules -4.7 %).  With 3 they fit in registers (an LDS copy measured
-  // 3.5 % slower), past 9 not in the LDS.
-  constexpr bool WIMG = KBM >= 6 && KBM <= 9;
+  constexpr bool WIMG = PAIR;       // the filter fragments in LDS
   // per wave 16 rows of 64 values for the per-edge sums, or 8 taken in two
   // passes beside the filter copy (+2: the rows' 16-byte groups start on
   // different banks)
   constexpr int RED_LD = 64 + 2, RROWS = WIMG ? 8 : 16;
   __shared__ __attribute__((aligned(16))) A red[NWB * RROWS * RED_LD];
   constexpr int WIMG_N = WIMG ? FTW * 3 * KBM * 64 : 2;
-  __shared__ __attribute__((aligned(16))) A wimg[NWB * WIMG_N];
+  __shared__ __attribute__((aligned(16))) A wimg[(WIMG ? NGW : 1) * WIMG_N];
   const __amdgpu_buffer_rsrc_t r_gs = buf_rsrc(gs, a.bg ? (size_t)a.N * F * sizeof(A) : 0);
   const __amdgpu_buffer_rsrc_t r_gv = buf_rsrc(gv, a.bg ? (size_t)a.N * 3 * F * sizeof(A) : 0);
   // the filter's MFMA B fragments: [3 parts x F / 16 tiles][KBM][64 lanes]
   static_assert(P::KPL == 1, "one filter value per lane and k-block");
   const __amdgpu_buffer_rsrc_t r_w = buf_rsrc(Wf, (size_t)3 * NFT * KBM * 64 * sizeof(T));
   const uint32_t lane_w = (uint32_t)lane * sizeof(T);
-  A* wi = wimg + (threadIdx.x >> 6) * WIMG_N;
+  A* wi = wimg + (WIMG ? wv % NGW : 0) * WIMG_N;
   if constexpr (WIMG) {
+    // fragment x of the group (tile, part, k-block) by stream x % NS
 #pragma unroll
-    for (int q = 0; q < FTW; ++q)
-#pragma unroll
-      for (int part = 0; part < 3; ++part)
-#pragma unroll
-        for (int kb = 0; kb < KBM; ++kb) {
-          const int ct = part * NFT + FTW * wave + q;
-          wi[((q * 3 + part) * KBM + kb) * 64 + lane] =
-              buf_ld8<A>(r_w, lane_w, (ct * KBM + kb) * 64 * (int)sizeof(T));
-        }
-    __builtin_amdgcn_wave_barrier();
+    for (int x = 0; x < FTW * 3 * KBM; ++x) {
+      if (x % NS != stream) continue;
+      const int q = x / (3 * KBM), part = x / KBM % 3, kb = x % KBM;
+      const int ch = chan(q, lane & 15);
+      const uint32_t off = (((uint32_t)(part * NFT + ch / 16) * KBM + kb) * 64 + (lane & 48) + ch % 16) * sizeof(T);
+      wi[x * 64 + lane] = buf_ld8<A>(r_w, off, 0);
+    }
+    __syncthreads();
   }
-  const int j0 = lb / SLICES * MB_RB;
+  const int j0 = (lb / SLICES * NS + stream) * MB_RB;
   if (j0 >= a.N) return;
   const int j1 = min(a.N, j0 + MB_RB);
   const int tp_lane = a.t_ptr[j0 + min(lane, j1 - j0)];
@@ -1226,7 +1236,7 @@ k_message_bwd(MsgBwdArgs a) {
       const size_t jb = (size_t)j * 3 * F;
 #pragma unroll
       for (int q = 0; q < FTW; ++q) {
-        const int ch = (FTW * wave + q) * 16 + lane;
+        const int ch = chan(q, lane);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
           gh_out[jb + k * F + ch] = A(0);
@@ -1241,32 +1251,50 @@ k_message_bwd(MsgBwdArgs a) {
   // The block's senders are walked as one stream of chunks of up to 16
   // edges of one sender; each chunk loads its operand rows and edge info at
   // its start.  Per lane: the A rows (position c0 + lane % 16; past the
-  // chunk the zero row E) and, for its 4 accumulator rows, edge id,
-  // receiver and rhat (past the chunk: receiver 0 and a zero filter, so
-  // they add nothing).
-  Fr Gan[KBM], Gdn[KBM];
-  int ern[4], irn[4];
-  A rhn[4][3];
+  // chunk the zero row E), and edge id, receiver and rhat of ONE row, 4 (lane
+  // % 4) + lane / 16 (past the chunk: receiver 0, rhat 0).  A lane's
+  // accumulator rows 4 i + lane / 16 are those of lane i of its quad: they
+  // reach it by quad broadcasts, without registers for four rows.
+  static_assert(P::PREC == PAINN_FP64, "accumulator rows 4 i + lane / 16");
+  Fr Ga[KBM], Gd[KBM];
+  int er = -1, ir = 0;
+  A rx = 0, ry = 0, rz = 0;
   auto prefetch = [&](int c0, int cnt) {
     const int erA = (lane & 15) < cnt ? c0 + (lane & 15) : (int)a.E;
     const T* gp = basis + (size_t)erA * kcols + (lane >> 4) * P::KPL;
     const T* dp = dbasis + (size_t)erA * kcols + (lane >> 4) * P::KPL;
+    const int row = 4 * (lane & 3) + (lane >> 4);
+    er = -1;
+    ir = 0;
+    rx = ry = rz = 0;
+    if (row < cnt) {
+      const A* ei = einfo + 4 * (size_t)(c0 + row);
+      const A2 e0 = *(const A2*)ei, e1 = *(const A2*)(ei + 2);
+      er = a.t_edge[c0 + row];
+      rx = e0[0];
+      ry = e0[1];
+      rz = e1[0];
+      ir = acc_index(e1[1]);
+    }
 #pragma unroll
     for (int kb = 0; kb < KBM; ++kb) {
-      Gan[kb] = P::frag(gp + kb * P::KC);
-      Gdn[kb] = P::frag(dp + kb * P::KC);
+      Ga[kb] = P::frag(gp + kb * P::KC);
+      Gd[kb] = P::frag(dp + kb * P::KC);
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = P::row(lane, i);
-      const bool ok = row < cnt;
-      const A* ei = einfo + 4 * (size_t)(ok ? c0 + row : 0);
-      ern[i] = ok ? a.t_edge[c0 + row] : -1;
-      irn[i] = ok ? acc_index(ei[3]) : 0;
-      rhn[i][0] = ok ? ei[0] : A(0);
-      rhn[i][1] = ok ? ei[1] : A(0);
-      rhn[i][2] = ok ? ei[2] : A(0);
-    }
+  };
+  // the value of lane i of this lane's quad (i a constant)
+  auto quad = [](A x, auto ic) {
+    constexpr int sel = decltype(ic)::value * 0x55;
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffff), sel, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), sel, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+  };
+  auto each_row = [](auto&& fn) {
+    fn(std::integral_constant<int, 0>{});
+    fn(std::integral_constant<int, 1>{});
+    fn(std::integral_constant<int, 2>{});
+    fn(std::integral_constant<int, 3>{});
   };
   int j = first_with_edges(j0);
   if (j >= j1) return;
@@ -1279,23 +1307,8 @@ k_message_bwd(MsgBwdArgs a) {
   while (true) {
     const size_t jb = (size_t)j * 3 * F;
     const int eb = tp(j + 1);
-    prefetch(c0, min(16, eb - c0));
-    Fr Ga[KBM], Gd[KBM];
-    int er[4], ir[4];
-    A rh[4][3];
-#pragma unroll
-    for (int kb = 0; kb < KBM; ++kb) {
-      Ga[kb] = Gan[kb];
-      Gd[kb] = Gdn[kb];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      er[i] = ern[i];
-      ir[i] = irn[i];
-      rh[i][0] = rhn[i][0];
-      rh[i][1] = rhn[i][1];
-      rh[i][2] = rhn[i][2];
-    }
+    const int cnt = min(16, eb - c0);
+    prefetch(c0, cnt);
     // the next chunk: this sender's next 16 edges, else the next sender
     // (found after this chunk, so that its indices are not live across the
     // matrix work)
@@ -1315,36 +1328,46 @@ k_message_bwd(MsgBwdArgs a) {
     // (32-bit offsets, no per-value select); otherwise the values are
     // selected away.
     A gsr[FTW][4], gvr[FTW][4][3];
+    // (PAIR: both tiles' values of a row are neighbours, one 16-byte load)
     if (a.bg) {
+      const uint32_t ch8 = (uint32_t)chan(0, lane & 15) * sizeof(A);
+      each_row([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const uint32_t ri = __builtin_amdgcn_mov_dpp(ir, i * 0x55, 0xf, 0xf, true);
+        const bool live = 4 * i + (lane >> 4) < cnt;
+        const uint32_t os = live ? ri * (uint32_t)(F * sizeof(A)) + ch8 : 0x80000000u;
+        const uint32_t ov = live ? ri * (uint32_t)(3 * F * sizeof(A)) + ch8 : 0x80000000u;
+        if constexpr (PAIR) {
+          const A2 s2 = buf_ld16<A2>(r_gs, os, 0);
+          for (int q = 0; q < FTW; ++q) gsr[q][i] = s2[q];
 #pragma unroll
-      for (int q = 0; q < FTW; ++q) {
-        const uint32_t ch8 = (uint32_t)((FTW * wave + q) * 16 + (lane & 15)) * sizeof(A);
+          for (int k = 0; k < 3; ++k) {
+            const A2 v2 = buf_ld16<A2>(r_gv, ov, k * F * (int)sizeof(A));
+            for (int q = 0; q < FTW; ++q) gvr[q][i][k] = v2[q];
+          }
+        } else {
+          gsr[0][i] = buf_ld8<A>(r_gs, os, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool live = er[i] >= 0;
-          const uint32_t os = live ? (uint32_t)ir[i] * (F * sizeof(A)) + ch8 : 0x80000000u;
-          const uint32_t ov = live ? (uint32_t)ir[i] * (3 * F * sizeof(A)) + ch8 : 0x80000000u;
-          gsr[q][i] = buf_ld8<A>(r_gs, os, 0);
-#pragma unroll
-          for (int k = 0; k < 3; ++k) gvr[q][i][k] = buf_ld8<A>(r_gv, ov, k * F * (int)sizeof(A));
+          for (int k = 0; k < 3; ++k) gvr[0][i][k] = buf_ld8<A>(r_gv, ov, k * F * (int)sizeof(A));
         }
-      }
+      });
     } else {
+      each_row([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const size_t ri = (uint32_t)__builtin_amdgcn_mov_dpp(ir, i * 0x55, 0xf, 0xf, true);
+        const bool live = 4 * i + (lane >> 4) < cnt;
 #pragma unroll
-      for (int q = 0; q < FTW; ++q) {
-        const int ch = (FTW * wave + q) * 16 + (lane & 15);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const size_t ib = (size_t)ir[i] * 3 * F;
-          const bool live = er[i] >= 0;
-          const A s0 = gs[(size_t)ir[i] * F + ch];
-          const A v0 = gv[ib + ch], v1 = gv[ib + F + ch], v2 = gv[ib + 2 * F + ch];
+        for (int q = 0; q < FTW; ++q) {
+          const int ch = chan(q, lane & 15);
+          const A s0 = gs[ri * F + ch];
           gsr[q][i] = live ? s0 : A(0);
-          gvr[q][i][0] = live ? v0 : A(0);
-          gvr[q][i][1] = live ? v1 : A(0);
-          gvr[q][i][2] = live ? v2 : A(0);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const A v0 = gv[ri * 3 * F + k * F + ch];
+            gvr[q][i][k] = live ? v0 : A(0);
+          }
         }
-      }
+      });
     }
     // The filter fragments are buffer loads: the lane's 8 bytes plus the
     // fragment's offset, a scalar (no per-load address arithmetic).  When
@@ -1354,65 +1377,100 @@ k_message_bwd(MsgBwdArgs a) {
     // (With the LDS copy the opaque offset keeps its reads in the loop.)
     int wofs = 0;
     if constexpr (WIMG || FTW * 3 * KBM * (int)sizeof(A) / 4 > 40) asm volatile("" : "+s"(wofs));
-    // per-edge partial sums: [dE/dd, dE/drhat x, y, z] x 4 rows
+    // per-edge partial sums: [dE/drhat x, y, z, dE/dd] x 4 rows
     A vals[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) vals[k] = 0;
-#pragma unroll
-    for (int q = 0; q < FTW; ++q) {
-      C w[3], wd[3];
-#pragma unroll
-      for (int part = 0; part < 3; ++part) {
-        for (int r = 0; r < 4; ++r) w[part][r] = wd[part][r] = 0;
-        if (L0 && part == 1) continue;
-#pragma unroll
-        for (int kb = 0; kb < KBM; ++kb) {
-          const int ct = part * NFT + FTW * wave + q;
-          Fr bw;
-          if constexpr (WIMG) bw = wi[wofs + ((q * 3 + part) * KBM + kb) * 64 + lane];
-          else bw = buf_ld8<Fr>(r_w, lane_w, wofs + (ct * KBM + kb) * 64 * (int)sizeof(T));
-          if (!L0 || part == 2) w[part] = P::mfma(Ga[kb], bw, w[part]);
-          wd[part] = P::mfma(Gd[kb], bw, wd[part]);
-        }
-      }
-      const int ch = (FTW * wave + q) * 16 + (lane & 15);
-      const A hs = P::ld(h[jb + ch]), hr = P::ld(h[jb + 2 * F + ch]);
-      const A hv = L0 ? A(0) : P::ld(h[jb + F + ch]);
-      const A v0 = L0 ? A(0) : P::ld(vv[jb + ch]), v1 = L0 ? A(0) : P::ld(vv[jb + F + ch]);
-      const A v2 = L0 ? A(0) : P::ld(vv[jb + 2 * F + ch]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const A g_s = gsr[q][i], g0 = gvr[q][i][0], g1 = gvr[q][i][1], g2 = gvr[q][i][2];
-        const A Ar = g0 * rh[i][0] + g1 * rh[i][1] + g2 * rh[i][2];
-        const A tr = hr * w[2][i];
-        if constexpr (L0) {
-          vals[i] += g_s * hs * wd[0][i] + Ar * hr * wd[2][i];
-        } else {
-          const A Av = g0 * v0 + g1 * v1 + g2 * v2;
-          acc_h[q][0] += g_s * w[0][i];
-          acc_h[q][1] += Av * w[1][i];
-          acc_h[q][2] += Ar * w[2][i];
-          const A tv = hv * w[1][i];
-          acc_v[q][0] += g0 * tv;
-          acc_v[q][1] += g1 * tv;
-          acc_v[q][2] += g2 * tv;
-          vals[i] += g_s * hs * wd[0][i] + Av * hv * wd[1][i] + Ar * hr * wd[2][i];
-        }
-        vals[4 + i] += g0 * tr;
-        vals[8 + i] += g1 * tr;
-        vals[12 + i] += g2 * tr;
-      }
-    }
-    // lane: the wave's total of value (lane % 16) / 4 for its row lane % 4,
-    // over the 16 lanes of its row group, through the wave's LDS rows (one
-    // write and read per value instead of a butterfly of selects and lane
+    // The wave's total of value (lane % 16) / 4 for the row of lane % 4, over
+    // the 16 lanes of its row group, through the wave's LDS rows (one write
+    // and read per value instead of a butterfly of selects and lane
     // shuffles).  16 rows: value k of every lane in row k, each lane sums 16
     // consecutive entries of its row.  8 rows: two passes, value 8 p + k in
     // row k; lane l sums entries 16 (l / 16) + 8 h .. + 7 (h = bit 3 of l)
     // of row l % 8 and one shuffle adds the other half, so value lane % 16
-    // is pass h's row lane % 8.
+    // is pass h's row lane % 8.  The first pass's values are complete after
+    // part r, which frees their registers for the rest.
+    A* rw = red + (threadIdx.x >> 6) * (RROWS * RED_LD);
+    auto pass8 = [&](int p) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) rw[k * RED_LD + lane] = vals[8 * p + k];
+      __builtin_amdgcn_wave_barrier();
+      const A* rr = rw + (lane & 7) * RED_LD + (lane >> 4) * 16 + ((lane >> 3) & 1) * 8;
+      A2 t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = *(const A2*)(rr + 2 * u);
+      __builtin_amdgcn_wave_barrier();
+      A sp = ((t[0][0] + t[0][1]) + (t[1][0] + t[1][1])) + ((t[2][0] + t[2][1]) + (t[3][0] + t[3][1]));
+      return sp + __shfl_xor(sp, 8);
+    };
+    // one part of the filter and its derivative for tile q
+    auto form = [&](int q, int part, C& w, C& wd, bool both) {
+      for (int r = 0; r < 4; ++r) w[r] = wd[r] = 0;
+#pragma unroll
+      for (int kb = 0; kb < KBM; ++kb) {
+        const int ct = part * NFT + FTW * wave + q;
+        Fr bw;
+        if constexpr (WIMG) bw = wi[wofs + ((q * 3 + part) * KBM + kb) * 64 + lane];
+        else bw = buf_ld8<Fr>(r_w, lane_w, wofs + (ct * KBM + kb) * 64 * (int)sizeof(T));
+        if (both) w = P::mfma(Ga[kb], bw, w);
+        wd = P::mfma(Gd[kb], bw, wd);
+      }
+    };
+    // (One part's accumulators at a time: left alone, the scheduler
+    // interleaves the parts and spills.)  Part r: A_r = g_v . rhat
+#pragma unroll
+    for (int q = 0; q < FTW; ++q) {
+      C w, wd;
+      form(q, 2, w, wd, true);
+      const A hr = P::ld(h[jb + 2 * F + chan(q, lane & 15)]);
+      each_row([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const A g0 = gvr[q][i][0], g1 = gvr[q][i][1], g2 = gvr[q][i][2];
+        const A Ar = g0 * quad(rx, ic) + g1 * quad(ry, ic) + g2 * quad(rz, ic);
+        const A tr = hr * w[i];
+        if constexpr (!L0) acc_h[q][2] += Ar * w[i];
+        vals[i] += g0 * tr;
+        vals[4 + i] += g1 * tr;
+        vals[8 + i] += g2 * tr;
+        vals[12 + i] += Ar * hr * wd[i];
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    A tot0 = 0;
+    if constexpr (RROWS == 8) tot0 = pass8(0);
+#pragma unroll
+    for (int q = 0; q < FTW; ++q) {
+      C w, wd;
+      const int ch = chan(q, lane & 15);
+      // part s
+      form(q, 0, w, wd, !L0);
+      const A hs = P::ld(h[jb + ch]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (!L0) acc_h[q][0] += gsr[q][i] * w[i];
+        vals[12 + i] += gsr[q][i] * hs * wd[i];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // part v: A_v = g_v . v_j
+      if constexpr (!L0) {
+        form(q, 1, w, wd, true);
+        const A hv = P::ld(h[jb + F + ch]);
+        const A v0 = P::ld(vv[jb + ch]), v1 = P::ld(vv[jb + F + ch]), v2 = P::ld(vv[jb + 2 * F + ch]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const A g0 = gvr[q][i][0], g1 = gvr[q][i][1], g2 = gvr[q][i][2];
+          const A Av = g0 * v0 + g1 * v1 + g2 * v2;
+          const A tv = hv * w[i];
+          acc_h[q][1] += Av * w[i];
+          acc_v[q][0] += g0 * tv;
+          acc_v[q][1] += g1 * tv;
+          acc_v[q][2] += g2 * tv;
+          vals[12 + i] += Av * hv * wd[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     {
-      A* rw = red + (threadIdx.x >> 6) * (RROWS * RED_LD);
       A sum = 0;
       if constexpr (RROWS == 16) {
 #pragma unroll
@@ -1426,28 +1484,13 @@ k_message_bwd(MsgBwdArgs a) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) sum += t[u][0] + t[u][1];
       } else {
-        const A* rr = rw + (lane & 7) * RED_LD + (lane >> 4) * 16 + ((lane >> 3) & 1) * 8;
-        A tot[2];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-#pragma unroll
-          for (int k = 0; k < 8; ++k) rw[k * RED_LD + lane] = vals[8 * p + k];
-          __builtin_amdgcn_wave_barrier();
-          A2 t[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) t[u] = *(const A2*)(rr + 2 * u);
-          __builtin_amdgcn_wave_barrier();
-          A sp = ((t[0][0] + t[0][1]) + (t[1][0] + t[1][1])) + ((t[2][0] + t[2][1]) + (t[3][0] + t[3][1]));
-          sp += __shfl_xor(sp, 8);
-          tot[p] = sp;
-        }
-        sum = (lane & 8) ? tot[1] : tot[0];
+        const A tot1 = pass8(1);
+        sum = (lane & 8) ? tot1 : tot0;
       }
-      const int k = lane & 15, i = k & 3;
-      const int e = i == 0 ? er[0] : i == 1 ? er[1] : i == 2 ? er[2] : er[3];
+      // (the row of value lane % 16 is this lane's own: 4 (lane % 4) + lane / 16)
       // one add per slot per launch, and launches run in layer order: the
       // sums are deterministic; the add does not return, so no wave waits
-      if (e >= 0) unsafeAtomicAdd(eg + ((size_t)e * NW + wave) * 4 + (k >> 2), sum);
+      if (er >= 0) unsafeAtomicAdd(eg + ((size_t)er * NW + wave) * 4 + ((((lane & 15) >> 2) + 1) & 3), sum);
     }
     find_next();
     if (last && !L0) {
@@ -1467,10 +1510,10 @@ k_message_bwd(MsgBwdArgs a) {
 #pragma unroll
         for (int q = 0; q < FTW; ++q)
 #pragma unroll
-          for (int k = 0; k < 3; ++k) gvj[q][k] = gv[jb + k * F + (FTW * wave + q) * 16 + lane];
+          for (int k = 0; k < 3; ++k) gvj[q][k] = gv[jb + k * F + chan(q, lane)];
 #pragma unroll
         for (int q = 0; q < FTW; ++q) {
-          const int ch = (FTW * wave + q) * 16 + lane;
+          const int ch = chan(q, lane);
 #pragma unroll
           for (int k = 0; k < 3; ++k) {
             gh_out[jb + k * F + ch] = acc_h[q][k];
@@ -1913,8 +1956,9 @@ void launch_message_bwd_kbm(hipStream_t st, const MsgBwdArgs& ma) {
     if (ma.first) k_message_bwd_lane<P, F, KBM, true><<<blocks, 64 * NWB, 0, st>>>(ma);
     else k_message_bwd_lane<P, F, KBM, false><<<blocks, 64 * NWB, 0, st>>>(ma);
   } else {
-    constexpr int NWB = mb_nwb<P, F, KBM>(), SLICES = F / 16 / mb_ftw<P, F, KBM>() / NWB;
-    const int blocks = (int)(((long long)(ma.N + MB_RB - 1) / MB_RB * SLICES + 7) / 8 * 8);
+    constexpr int NWB = mb_nwb<P, F, KBM>(), NS = mb_ns<P, F, KBM>();
+    constexpr int SLICES = F / 16 / mb_ftw<P, F, KBM>() / mb_ngw<P, F, KBM>();
+    const int blocks = (int)(((long long)(ma.N + MB_RB * NS - 1) / (MB_RB * NS) * SLICES + 7) / 8 * 8);
     if (ma.first) k_message_bwd<P, F, KBM, true><<<blocks, 64 * NWB, 0, st>>>(ma);
     else k_message_bwd<P, F, KBM, false><<<blocks, 64 * NWB, 0, st>>>(ma);
   }
@@ -1926,7 +1970,7 @@ void launch_message_bwd_kbm(hipStream_t st, const MsgBwdArgs& ma) {
 template <class P, int F>
 int message_bwd_slots(int nkb) {
   if constexpr (sizeof(typename P::T) == 4) return F / 64;
-  return F / 16 / (nkb == 3 ? mb_ftw<P, F, 3>() : mb_ftw<P, F, 6>());
+  return F / 16 / (nkb <= 9 ? mb_ftw<P, F, 9>() : mb_ftw<P, F, 12>());
 }
 
 template <class P, int F>
