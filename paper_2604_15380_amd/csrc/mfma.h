@@ -39,14 +39,16 @@ __device__ __forceinline__ bf16_t f_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
-// The three bf16 planes of an FP32 value (upper 16 bits each).  A NaN keeps
+// The three bf16 planes of an FP32 value (upper 16 bits each), hi and mid
+// rounded to nearest so that what is left has either sign.  A NaN keeps
 // its hi plane (quiet), an infinity too; their lower planes are zero.
 __device__ __forceinline__ void split3(float x, uint32_t* p) {
   const uint32_t u = __float_as_uint(x);
   const bool fin = (u & 0x7f800000u) != 0x7f800000u;
-  const uint32_t h = u & 0xffff0000u;
+  // (the largest values, which would round to infinity, are cut off instead)
+  const uint32_t h = ((u & 0x7fffffffu) < 0x7f7f8000u ? u + 0x8000u : u) & 0xffff0000u;
   const float r1 = x - __uint_as_float(h);
-  const uint32_t m = __float_as_uint(r1) & 0xffff0000u;
+  const uint32_t m = (__float_as_uint(r1) + 0x8000u) & 0xffff0000u;
   const float r2 = r1 - __uint_as_float(m);
   p[0] = fin ? h : (h | ((u & 0x007fffffu) ? 0x00400000u : 0u));
   p[1] = fin ? m : 0u;

@@ -164,12 +164,13 @@ hipError_t pack_branch(PrecModel* pm, int prec, const double* W, int dout, int d
             for (int p = 0; p < 3; ++p) {
               uint32_t u;
               memcpy(&u, &r, 4);
+              if ((u & 0x7fffffffu) < 0x7f7f8000u) u += 0x8000u;
               u &= 0xffff0000u;
               const uint16_t hi = (uint16_t)(u >> 16);
               memcpy(&wh[(blk + p) * 1024 + (size_t)l * 16 + e * 2], &hi, 2);
               float f;
               memcpy(&f, &u, 4);
-              r -= f;
+              r = std::isfinite(r) ? r - f : 0.0f;
             }
           } else {
             const bf16_t h = to_bf16(x);
