@@ -39,7 +39,8 @@ ELEM = {"fp64": 8, "fp32": 4, "bf16": 2}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 # the kernel sources a stored traffic measurement depends on (per mode)
 KERNEL_SOURCES = ["paper_2604_15380_amd/csrc/forward.hip", "paper_2604_15380_amd/csrc/mfma.h",
-                  "paper_2604_15380_amd/csrc/neighbors.hip"]
+                  "paper_2604_15380_amd/csrc/neighbors.hip", "paper_2604_15380_amd/csrc/rows.h",
+                  "paper_2604_15380_amd/csrc/branch.hip", "paper_2604_15380_amd/csrc/branchgemm.h"]
 KERNEL_SOURCES_FORCES = KERNEL_SOURCES + ["paper_2604_15380_amd/csrc/backward.hip"]
 
 
@@ -55,7 +56,8 @@ def source_digest(forces: bool = False) -> str:
     return h.hexdigest()[:16]
 
 
-def kernel_work(kernel: str, hp, N: int, E: int, prec: str, head_entries: int | None = None):
+def kernel_work(kernel: str, hp, N: int, E: int, prec: str, head_entries: int | None = None,
+                forces: bool = False):
     """Algorithmic work of ONE launch of a kernel class:
     (compute unit, flops on the matrix cores, flops on the vector ALU, HBM bytes).
 
@@ -83,7 +85,12 @@ def kernel_work(kernel: str, hp, N: int, E: int, prec: str, head_entries: int | 
     bwd_phi: per atom 10 F^2 (W1 s recomputed, W2^T, W1^T).
     bwd_heads: per (atom, head) entry twice the heads' forward flops of every
              layer but the 1-wide output (the pre-activations recomputed, then
-             the transposed layers).
+             the transposed layers).  Branches with a hidden layer of 256 or
+             more: the heads' launches run the branches' transposed layers too
+             (once the forward flops of their hidden layers), and bwd_heads the
+             shared layers only, per atom.  Their FP32 products run on the BF16
+             matrix cores (six per FP32 product), so `frac` of the FP32 peak
+             can pass 1.
     """
     F, K, L = hp.F, hp.K, hp.L
     b = ELEM[prec]
@@ -104,14 +111,19 @@ def kernel_work(kernel: str, hp, N: int, E: int, prec: str, head_entries: int | 
         return "mfma", N * 22.0 * F * F, 0.0, N * (9.0 * F * b + 8.0 * F * ab)
     if kernel == "bwd_phi":
         return "mfma", N * 10.0 * F * F, 0.0, N * (F * b + 6.0 * F * ab)
+    wide = max(list(hp.branch_dims)[:-1], default=0) >= 256
     if kernel == "bwd_heads":
-        dims = [F] + list(hp.shared_dims) + list(hp.branch_dims)[:-1]
-        n = N if head_entries is None else head_entries
+        dims = [F] + list(hp.shared_dims) + ([] if wide else list(hp.branch_dims)[:-1])
+        n = N if wide or head_entries is None else head_entries
         return "mfma", n * 2.0 * sum(2.0 * a * c for a, c in zip(dims[:-1], dims[1:])), 0.0, N * F * b
     if kernel == "heads":
         dims = [F] + list(hp.shared_dims) + list(hp.branch_dims)
         n = N if head_entries is None else head_entries
-        return "mfma", n * sum(2.0 * a * c for a, c in zip(dims[:-1], dims[1:])), 0.0, N * F * b
+        fl = sum(2.0 * a * c for a, c in zip(dims[:-1], dims[1:]))
+        if forces and wide:
+            back = dims[len(hp.shared_dims):-1]
+            fl += sum(2.0 * a * c for a, c in zip(back[:-1], back[1:]))
+        return "mfma", n * fl, 0.0, N * F * b
     return None, 0.0, 0.0, 0.0
 
 
@@ -543,7 +555,7 @@ def main():
         digest = source_digest(args.forces)
         for kern, (ms, launches) in prof.items():
             # work summed over the batches the timed pass walked, per launch
-            works = [kernel_work(kern, hp, batches[k].n_atoms, e, prec, head_entries)
+            works = [kernel_work(kern, hp, batches[k].n_atoms, e, prec, head_entries, args.forces)
                      for k, e in zip(order, edges)]
             if not works[0][0]:
                 continue
