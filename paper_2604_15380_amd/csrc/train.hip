@@ -627,39 +627,62 @@ __global__ void k_tr_upd_bwd2(int N, int F, const S* __restrict__ g_in, const S*
 // head): perm[p] = atom, hstart[h] = first slot of head h, hstart[H] = slots
 // in use; atoms of a structure whose id is outside [0, H) get no slot and
 // set *bad.
-// One workgroup: every structure's first slot by counting the atoms before it
-// (first[b]), then the atoms in parallel.
-__global__ void __launch_bounds__(256) k_tr_group(int B, int N, int H, const int32_t* __restrict__ struct_ptr,
-                                                  const int32_t* __restrict__ atom_struct,
-                                                  const int32_t* __restrict__ dataset_id, int32_t* __restrict__ perm,
+// One workgroup finds every structure's first slot (first[b], -1: none), 256
+// structures at a time: its head's first slot, its head's atoms in the chunks
+// before (next[h]) and before it in its own chunk.  Linear in the structures:
+// with every structure's predecessors counted over the whole batch a step on
+// 16,384 structures of 5 to 20 atoms (F = 64) took 285 ms, now 159.
+__global__ void __launch_bounds__(256) k_tr_group(int B, int H, const int32_t* __restrict__ struct_ptr,
+                                                  const int32_t* __restrict__ dataset_id,
                                                   int32_t* __restrict__ hstart, int32_t* __restrict__ bad,
                                                   int32_t* __restrict__ first) {
-  __shared__ int nbad;
-  if (threadIdx.x == 0) nbad = 0;
+  __shared__ int next[HEADS_MAX], nbad;
+  __shared__ int2 chunk[256];                      // head (-1: none) and atoms
+  const int tid = threadIdx.x;
+  if (tid < HEADS_MAX) next[tid] = 0;
+  if (tid == 0) nbad = 0;
   __syncthreads();
-  // (head H stands for the end of the last one)
-  for (int x = threadIdx.x; x < B + H + 1; x += 256) {
-    const int b = x - (H + 1);
-    const int d = b < 0 ? x : dataset_id ? dataset_id[b] : 0;
+  auto at = [&](int b) {
+    const int d = b >= B ? -1 : dataset_id ? dataset_id[b] : 0;
+    return d < 0 || d >= H ? int2{-1, 0} : int2{d, struct_ptr[b + 1] - struct_ptr[b]};
+  };
+  for (int b = tid; b < B; b += 256) {
+    const int2 x = at(b);
+    if (x.x < 0) atomicAdd(&nbad, 1);
+    else atomicAdd(&next[x.x], x.y);
+  }
+  __syncthreads();
+  if (tid == 0) {
     int slot = 0;
-    for (int q = 0; q < B; ++q) {
-      const int dq = dataset_id ? dataset_id[q] : 0;
-      if (dq < 0 || dq >= H) continue;
-      if (dq < d || (dq == d && q < b)) slot += struct_ptr[q + 1] - struct_ptr[q];
+    for (int h = 0; h < H; ++h) {
+      const int n = next[h];
+      hstart[h] = next[h] = slot;
+      slot += n;
     }
-    if (b < 0) {
-      hstart[x] = slot;
-    } else {
-      first[b] = d < 0 || d >= H ? -1 : slot;
-      if (d < 0 || d >= H) atomicAdd(&nbad, 1);
-    }
+    hstart[H] = slot;
+    *bad = nbad;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) *bad = nbad;
-  for (int a = threadIdx.x; a < N; a += 256) {
-    const int b = atom_struct[a], f = first[b];
-    if (f >= 0) perm[f + a - struct_ptr[b]] = a;
+  for (int b0 = 0; b0 < B; b0 += 256) {
+    const int2 x = at(b0 + tid);
+    __syncthreads();
+    chunk[tid] = x;
+    __syncthreads();
+    int slot = x.x < 0 ? -1 : next[x.x];
+    if (x.x >= 0)
+      for (int q = 0; q < tid; ++q)
+        if (chunk[q].x == x.x) slot += chunk[q].y;
+    if (b0 + tid < B) first[b0 + tid] = slot;
+    __syncthreads();
+    if (x.x >= 0) atomicAdd(&next[x.x], x.y);
   }
+}
+
+__global__ void k_tr_perm(int N, const int32_t* __restrict__ struct_ptr, const int32_t* __restrict__ atom_struct,
+                          const int32_t* __restrict__ first, int32_t* __restrict__ perm) {
+  const int a = blockIdx.x * TB + threadIdx.x;
+  if (a >= N) return;
+  const int b = atom_struct[a], f = first[b];
+  if (f >= 0) perm[f + a - struct_ptr[b]] = a;
 }
 
 template <class S>
@@ -1093,8 +1116,11 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     y = (const S*)w.shy[m];
     dy = hp.shared_dims[m];
   }
-  if (REAL) k_tr_group<<<1, 256, 0, st>>>(B, N, H, g->struct_ptr, g->atom_struct, dataset_id, w.perm, w.hstart,
-                                          w.bad, (int32_t*)w.c);   // c is written by the loss, later
+  if (REAL) {
+    int32_t* first = (int32_t*)w.c;                // c is written by the loss, later
+    k_tr_group<<<1, 256, 0, st>>>(B, H, g->struct_ptr, dataset_id, w.hstart, w.bad, first);
+    k_tr_perm<<<blocks((size_t)N), TB, 0, st>>>(N, g->struct_ptr, g->atom_struct, first, w.perm);
+  }
   const int32_t* slots = w.hstart + H;
   k_tr_gather<S><<<blocks((size_t)N * dy), TB, 0, st>>>(N, dy, slots, w.perm, y, (S*)w.yg);
   Heads heads;
