@@ -95,6 +95,8 @@ constexpr int TB = 256;
 inline unsigned blocks(size_t n, int t = TB) { return (unsigned)((n + t - 1) / t); }
 // most row chunks of one weight-gradient reduction (k_tr_wgrad)
 constexpr int WG_CHUNKS = 32;
+// workgroups below which a grouped weight gradient cuts its heads' rows
+constexpr size_t WG_FILL = 512;
 
 // ---- dense layers ------------------------------------------------------------
 // FP64 matrix-core tiles (v_mfma_f64_16x16x4f64: lane l holds A row l % 16 and
@@ -200,23 +202,24 @@ __global__ void __launch_bounds__(256) k_tr_dense(int rows, const int32_t* __res
 // Gb[o] = tangent( sum_r sc[r] A[r][o] ) (sc may be null: 1).  The tangent of a
 // product is A.v B.d + A.d B.v: two matrix products.  64 x 64 output tiles, a
 // 32 x 32 quarter per wave, 16 rows per step through LDS (the next 16 loaded
-// meanwhile).  One head's layer: gridDim.z cuts the rows into chunks of `rch`
-// whose partial sums go to Pz[z][o][kb] (kb < dinb), and k_tr_wgrad_sum adds
-// the chunks in order.  Several heads (hs > 0): gridDim.z is the head, whose
-// rows go through one workgroup per tile straight into G and Gb.  Either way
-// the result does not depend on scheduling.  Sums of 64 rows are added up
-// apart: one running sum over a head's hundreds of equal bias terms had four
-// times the rounding error.
+// meanwhile).  gridDim.z = heads x nz: each head's rows (heads' weights lie hs
+// apart) are cut into nz chunks of whole 64s, whose partial sums go to
+// Pz[head][z][o][kb] (kb < dinb), and k_tr_wgrad_sum adds the chunks in order;
+// one chunk (Pz null) goes straight into G and Gb.  Either way the result does
+// not depend on scheduling.  Sums of 64 rows are added up apart: one running
+// sum over a head's hundreds of equal bias terms had four times the rounding
+// error.
 constexpr int TG_T = 64, TG_R = 16, TG_LD = 80;              // LD: 16 x 2 reads in distinct banks
 __global__ void __launch_bounds__(256) k_tr_wgrad(int rows, const int32_t* __restrict__ range, int dout, int din,
-                                                  int dinb, int rch, long long hs, const Dual* __restrict__ A,
-                                                  int lda, const Dual* __restrict__ Bm, int ldb,
-                                                  const Dual* __restrict__ sc, double* __restrict__ Pz,
-                                                  double* __restrict__ G, double* __restrict__ Gb) {
+                                                  int dinb, int nz, long long hs, const Dual* __restrict__ A, int lda,
+                                                  const Dual* __restrict__ Bm, int ldb, const Dual* __restrict__ sc,
+                                                  double* __restrict__ Pz, double* __restrict__ G,
+                                                  double* __restrict__ Gb) {
   __shared__ double As[2][TG_R * TG_LD], Bs[2][TG_R * TG_LD];
-  const int head = hs ? blockIdx.z : 0, z = hs ? 0 : blockIdx.z;
+  const int head = blockIdx.z / nz, z = blockIdx.z % nz;
   const int lo0 = range ? range[head] : 0, hi0 = range ? range[head + 1] : rows;
-  const int lo = hs ? lo0 : lo0 + z * rch, hi = hs ? hi0 : min(hi0, lo + rch);
+  const int rch = ((hi0 - lo0 + nz - 1) / nz + 63) & ~63;
+  const int lo = min(hi0, lo0 + z * rch), hi = min(hi0, lo + rch);
   const int k0 = blockIdx.x * TG_T, o0 = blockIdx.y * TG_T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int NQ = TG_R * TG_T / 256;
@@ -283,7 +286,7 @@ __global__ void __launch_bounds__(256) k_tr_wgrad(int rows, const int32_t* __res
     }
   }
   flush();
-  double* P = Pz ? Pz + (size_t)z * dout * dinb : nullptr;
+  double* P = Pz ? Pz + (size_t)blockIdx.z * dout * dinb : nullptr;
   if (!P) {
     G += (long long)head * hs;
     if (Gb) Gb += (long long)head * hs;
@@ -304,16 +307,18 @@ __global__ void __launch_bounds__(256) k_tr_wgrad(int rows, const int32_t* __res
 }
 
 // G[o][k] = sum over the chunks z (in order) of Pz[z][o][k], k < din; the
-// bias column k = din (when dinb > din) into Gb[o].
-__global__ void k_tr_wgrad_sum(int nz, int dout, int din, int dinb, const double* __restrict__ Pz,
+// bias column k = din (when dinb > din) into Gb[o].  Head blockIdx.y.
+__global__ void k_tr_wgrad_sum(int nz, int dout, int din, int dinb, long long hs, const double* __restrict__ Pz,
                                double* __restrict__ G, double* __restrict__ Gb) {
   const size_t idx = (size_t)blockIdx.x * TB + threadIdx.x;
   if (idx >= (size_t)dout * dinb) return;
   const int o = (int)(idx / dinb), k = (int)(idx % dinb);
+  Pz += (size_t)blockIdx.y * nz * dout * dinb;
   double acc = 0.0;
   for (int z = 0; z < nz; ++z) acc += Pz[(size_t)z * dout * dinb + idx];
-  if (k < din) G[(size_t)o * din + k] = acc;
-  else Gb[o] = acc;
+  const long long h = (long long)blockIdx.y * hs;
+  if (k < din) G[h + (size_t)o * din + k] = acc;
+  else Gb[h + o] = acc;
 }
 
 // Y[r][o] *= silu'(Z[r][o]) for rows [lo, hi), width n (row strides ld).
@@ -897,6 +902,7 @@ struct TrWs {
   // loss
   double *E, *Fo, *c, *dpos, *lossbuf;
   double* wsum;   // partial sums of the weight-gradient reductions
+  size_t wsum_n;  // their count
 };
 
 constexpr size_t DS = sizeof(double) * 2;   // bytes per element, sized for Dual
@@ -996,7 +1002,8 @@ size_t carve(TrWs* w, char* base, const Hyper& hp, int N, long long E, int B) {
   const long long rmax = (long long)3 * N > (long long)E ? (long long)3 * N : (long long)E;
   long long nzmax = (rmax + 255) / 256;
   nzmax = nzmax < 1 ? 1 : nzmax > WG_CHUNKS ? WG_CHUNKS : nzmax;
-  w->wsum = (double*)take((size_t)nzmax * widest, 8);
+  w->wsum_n = (size_t)nzmax * widest;
+  w->wsum = (double*)take(w->wsum_n, 8);
   return off;
 }
 
@@ -1043,21 +1050,33 @@ inline int wg_chunks(long long rows) {
 
 // Weight (and bias) gradient of a layer stored [dout, din] at wofs (bias at
 // *bofs), reducing over `rows` rows of A and B, or of each of several heads
-// over its range.
-void wgrad(hipStream_t st, double* G, double* scratch, int rows, const int32_t* range, int dout, int din,
+// over its range; `scratch` holds `cap` partial sums.
+//
+// Several heads' rows are cut only while their tiles bring fewer than WG_FILL
+// workgroups.  Uncut, a 64-wide layer of two heads ran two workgroups over all
+// rows: 16,384 structures (205,000 atoms, F = 64) two heads 179 -> 157 ms a
+// step, 16 heads 160 -> 158.  Above the line cutting only adds the launch of
+// the sums (lead model, 208 to 2,704 tiles a layer: 4 structures 3.19 -> 3.20
+// ms, 100 structures 31.0 -> 30.7).
+void wgrad(hipStream_t st, double* G, double* scratch, size_t cap, int rows, const int32_t* range, int dout, int din,
            const Dual* A, int lda, const Dual* Bm, int ldb, size_t wofs, const size_t* bofs, const Dual* sc = nullptr,
            Heads hd = {}) {
   const int dinb = din + (bofs ? 1 : 0);
-  const int nz = hd.n > 1 ? 1 : wg_chunks(rows);
-  const int rch = (rows + nz - 1) / nz;
+  const unsigned tx = (unsigned)(dinb + TG_T - 1) / TG_T, ty = (unsigned)(dout + TG_T - 1) / TG_T;
+  int nz = wg_chunks(rows);
+  if (hd.n > 1) {
+    const size_t wgs = (size_t)tx * ty * hd.n, room = cap / ((size_t)hd.n * dout * dinb);
+    const size_t fill = wgs < WG_FILL ? WG_FILL / wgs : 1;
+    if ((size_t)nz > fill) nz = (int)fill;
+    if ((size_t)nz > room) nz = room < 1 ? 1 : (int)room;
+  }
   const bool direct = nz == 1;
-  k_tr_wgrad<<<dim3((unsigned)((dinb + TG_T - 1) / TG_T), (unsigned)((dout + TG_T - 1) / TG_T),
-                    (unsigned)(hd.n > 1 ? hd.n : nz)),
-               256, 0, st>>>(rows, range, dout, din, dinb, rch < 1 ? 1 : rch, hd.n > 1 ? hd.stride : 0, A, lda, Bm,
-                             ldb, sc, direct ? nullptr : scratch, G + wofs, bofs ? G + *bofs : nullptr);
+  k_tr_wgrad<<<dim3(tx, ty, (unsigned)(hd.n * nz)), 256, 0, st>>>(rows, range, dout, din, dinb, nz, hd.stride, A, lda,
+                                                                 Bm, ldb, sc, direct ? nullptr : scratch, G + wofs,
+                                                                 bofs ? G + *bofs : nullptr);
   if (!direct)
-    k_tr_wgrad_sum<<<blocks((size_t)dout * dinb), TB, 0, st>>>(nz, dout, din, dinb, scratch, G + wofs,
-                                                              bofs ? G + *bofs : nullptr);
+    k_tr_wgrad_sum<<<dim3(blocks((size_t)dout * dinb), (unsigned)hd.n), TB, 0, st>>>(
+        nz, dout, din, dinb, hd.stride, scratch, G + wofs, bofs ? G + *bofs : nullptr);
 }
 
 // One pass.  Real (S = double): E, F into w.E, w.Fo.  Tangent (S = Dual, with
@@ -1152,7 +1171,7 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     const int dout = hp.branch_dims[m], din = m > 0 ? hp.branch_dims[m - 1] : dy;
     const S* xin = m > 0 ? (const S*)w.bry[m - 1] : (const S*)w.yg;
     if constexpr (!REAL)
-      wgrad(st, G, w.wsum, N, w.hstart, dout, din, gcur, dout, xin, din, L.branch_w[0][m], &L.branch_b[0][m], nullptr,
+      wgrad(st, G, w.wsum, w.wsum_n, N, w.hstart, dout, din, gcur, dout, xin, din, L.branch_w[0][m], &L.branch_b[0][m], nullptr,
             heads);
     dense_t<S>(st, th, N, w.hstart, dout, din, gcur, dout, L.branch_w[0][m], gnext, din, (const S*)nullptr, 0, heads);
     if (m > 0)
@@ -1174,7 +1193,7 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     const int dout = hp.shared_dims[m], din = m > 0 ? hp.shared_dims[m - 1] : F;
     const S* xin = m > 0 ? (const S*)w.shy[m - 1] : (const S*)w.sL;
     k_tr_mul_dsilu<S><<<blocks((size_t)N * dout), TB, 0, st>>>(N, nullptr, dout, gcur, dout, (const S*)w.shz[m], dout);
-    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, dout, din, gcur, dout, xin, din, L.shared_w[m], &L.shared_b[m]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, w.wsum_n, N, nullptr, dout, din, gcur, dout, xin, din, L.shared_w[m], &L.shared_b[m]);
     dense_t<S>(st, th, N, nullptr, dout, din, gcur, dout, L.shared_w[m], gnext, din);
     S* t = gcur;
     gcur = gnext;
@@ -1196,16 +1215,16 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
     // update block: (gs, gv) at s', v' -> (gs2, gv2) at s_mid, v_mid
     k_tr_upd_bwd1<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, F, gs, gv, (S*)w.U[l], (S*)w.V[l], (S*)w.a[l],
                                                            (S*)w.ga, (S*)w.gU, (S*)w.gV);
-    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F3, F, (S*)w.ga, F3, (S*)w.aa[l], F, a[A_UPD_W2], &a[A_UPD_B2]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, w.wsum_n, N, nullptr, F3, F, (S*)w.ga, F3, (S*)w.aa[l], F, a[A_UPD_W2], &a[A_UPD_B2]);
     dense_t<S>(st, th, N, nullptr, F3, F, (S*)w.ga, F3, a[A_UPD_W2], (S*)w.gaa, F);
     k_tr_mul_dsilu<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, nullptr, F, (S*)w.gaa, F, (S*)w.za[l], F);
-    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F, 2 * F, (S*)w.gaa, F, (S*)w.xin[l], 2 * F, a[A_UPD_W1], &a[A_UPD_B1]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, w.wsum_n, N, nullptr, F, 2 * F, (S*)w.gaa, F, (S*)w.xin[l], 2 * F, a[A_UPD_W1], &a[A_UPD_B1]);
     dense_t<S>(st, th, N, nullptr, F, 2 * F, (S*)w.gaa, F, a[A_UPD_W1], (S*)w.gin, 2 * F);
     k_tr_upd_bwd2<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, F, (S*)w.gin, (S*)w.xin[l], (S*)w.V[l], gs,
                                                            (S*)w.gV, gs2);
     if constexpr (!REAL) {
-      wgrad(st, G, w.wsum, 3 * N, nullptr, F, F, (S*)w.gU, F, (S*)w.vmid[l], F, a[A_U], nullptr);
-      wgrad(st, G, w.wsum, 3 * N, nullptr, F, F, (S*)w.gV, F, (S*)w.vmid[l], F, a[A_V], nullptr);
+      wgrad(st, G, w.wsum, w.wsum_n, 3 * N, nullptr, F, F, (S*)w.gU, F, (S*)w.vmid[l], F, a[A_U], nullptr);
+      wgrad(st, G, w.wsum, w.wsum_n, 3 * N, nullptr, F, F, (S*)w.gV, F, (S*)w.vmid[l], F, a[A_V], nullptr);
     }
     dense_t<S>(st, th, 3 * N, nullptr, F, F, (S*)w.gU, F, a[A_U], gv2, F, gv, F);
     dense_t<S>(st, th, 3 * N, nullptr, F, F, (S*)w.gV, F, a[A_V], gv2, F, gv2, F);
@@ -1222,14 +1241,14 @@ hipError_t run_pass(hipStream_t st, painn_trainer* tr, const painn_graph* g, con
                                                                w.dfc, (const double*)gv2, (const double*)w.gw, w.gd,
                                                                w.grh);
       } else {
-        wgrad(st, G, w.wsum, (int)E, nullptr, F3, K, (S*)w.gw, F3, (S*)w.basis, K, a[A_FILT_W], &a[A_FILT_B], (S*)w.fc);
+        wgrad(st, G, w.wsum, w.wsum_n, (int)E, nullptr, F3, K, (S*)w.gw, F3, (S*)w.basis, K, a[A_FILT_W], &a[A_FILT_B], (S*)w.fc);
       }
     }
     // phi: dE/dh -> dE/ds before the message (its residual gs2 added)
-    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F3, F, (S*)w.gh, F3, (S*)w.a1[l], F, a[A_PHI_W2], &a[A_PHI_B2]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, w.wsum_n, N, nullptr, F3, F, (S*)w.gh, F3, (S*)w.a1[l], F, a[A_PHI_W2], &a[A_PHI_B2]);
     dense_t<S>(st, th, N, nullptr, F3, F, (S*)w.gh, F3, a[A_PHI_W2], (S*)w.ga1, F);
     k_tr_mul_dsilu<S><<<blocks((size_t)N * F), TB, 0, st>>>(N, nullptr, F, (S*)w.ga1, F, (S*)w.z1[l], F);
-    if constexpr (!REAL) wgrad(st, G, w.wsum, N, nullptr, F, F, (S*)w.ga1, F, (S*)w.s[l], F, a[A_PHI_W1], &a[A_PHI_B1]);
+    if constexpr (!REAL) wgrad(st, G, w.wsum, w.wsum_n, N, nullptr, F, F, (S*)w.ga1, F, (S*)w.s[l], F, a[A_PHI_W1], &a[A_PHI_B1]);
     dense_t<S>(st, th, N, nullptr, F, F, (S*)w.ga1, F, a[A_PHI_W1], gs, F, gs2, F);
   }
   if (!REAL)

@@ -1,7 +1,8 @@
-"""The training step's grouping of atoms by head on batches of many
-structures: against the training oracle as in tests/test_gpu_train.py (loss
-1e-12, gradient 1e-9 of each array's largest), and that a step's time grows
-with the batch no faster than the batch."""
+"""The training step's grouping of atoms by head and the grouped weight
+gradients on batches of many structures and of many rows per head: against
+the training oracle as in tests/test_gpu_train.py (loss 1e-12, gradient 1e-9
+of each array's largest), and that a step's time grows with the batch no
+faster than the batch, and with a second head hardly at all."""
 import numpy as np
 import pytest
 import torch
@@ -55,6 +56,22 @@ def test_train_many_structures(rt, n_heads, per_head, empty):  # noqa: F811
     step(rt, hp, batch, f"{batch.n_struct} structures, {n_heads} heads")
 
 
+# grouped weight gradients cut each head's rows into chunks of whole 64s: the
+# rows on one head, next to the edges of the chunks, and a head with one row
+@pytest.mark.parametrize("n_mol,per", [(41, 25), (64, 16), (65, 16), (513, 2)])
+def test_train_few_heads_many_rows(rt, n_mol, per):  # noqa: F811
+    say(f"grouped weight gradients, {n_mol} molecules of {per} atoms on two heads")
+    hp = synth.HyperParams(F=8, K=4, L=1, n_species=4, n_heads=2, cutoff=2.0, branch_dims=[33, 1])
+    rng = np.random.default_rng(per)
+    structs = []
+    for k in range(n_mol):
+        n = 1 if k == 3 else per
+        grid = np.stack(np.meshgrid(*[np.arange(3)] * 3), -1).reshape(-1, 3)[:n] * 1.6
+        structs.append((grid + rng.uniform(-0.2, 0.2, (n, 3)), rng.integers(0, 4, n), np.zeros((3, 3)),
+                        np.zeros(3, np.uint8), 1 if k == 3 else 0))
+    step(rt, hp, synth.concat(structs), f"{n_mol} x {per} atoms, two heads")
+
+
 def step_ms(rt, n_struct, n_heads, atoms):  # noqa: F811
     from paper_2604_15380_amd import binding as B
     hp = synth.HyperParams(F=8, K=4, L=1, n_species=4, n_heads=n_heads, cutoff=2.0, branch_dims=[64, 1])
@@ -94,3 +111,10 @@ def test_train_step_time_linear_in_structures(rt):  # noqa: F811
     over every pair of structures took 40 times as long here)."""
     few, many = step_ms(rt, 2048, 4, 2), step_ms(rt, 16384, 4, 2)
     assert many <= 12 * few, (few, many)
+
+
+def test_train_second_head_is_cheap(rt):  # noqa: F811
+    """The same rows on two heads instead of one (with each head's rows in one
+    workgroup per tile: 1.5 times as long)."""
+    one, two = step_ms(rt, 20000, 1, 8), step_ms(rt, 20000, 2, 8)
+    assert two <= 1.25 * one, (one, two)
