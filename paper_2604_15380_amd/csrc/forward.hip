@@ -1854,6 +1854,7 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
   ha.ns = (int)pm->shared.size();
   // wide branches: this kernel runs the shared layers only
   const bool wide_branch = pm->branch_table != nullptr;
+  const bool small = branch_small(P::PREC, hp, N, fa.blend, fa.skip);
   ha.nb = wide_branch ? 0 : (int)hp.branch_dims.size();
   ha.y_out = nullptr;
   ha.ky = 0;
@@ -1940,7 +1941,7 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
     const A* hw = fa.blend ? (const A*)fa.hw : nullptr;
     const A skip = (A)fa.skip;
     const int nb256 = (N + 255) / 256;
-    const int TMP = !wide_branch ? TM : N < BRANCH_SMALL_ATOMS ? BRANCH_TM_SMALL : BRANCH_TM;
+    const int TMP = !wide_branch ? TM : small ? BRANCH_TM_SMALL : BRANCH_TM;
     k_head_clear<<<1, 64, 0, st>>>(plan);
     k_head_count<A><<<nb256, 256, 0, st>>>(N, H, fa.dataset_id, hw, skip, fa.g->atom_struct, plan, (A*)fa.e);
     k_head_plan<<<1, 64, 0, st>>>(H, TMP, plan, tiles);
@@ -1989,7 +1990,7 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
     b.branch_dims = &hp.branch_dims;
     b.N = N;
     b.H = H;
-    b.small = N < BRANCH_SMALL_ATOMS;
+    b.small = small;
     b.tiles = ha.tiles;
     b.plan = ha.plan;
     b.order = ha.order;

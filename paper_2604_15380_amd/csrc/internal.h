@@ -378,9 +378,21 @@ inline bool branch_wide(const Hyper& hp) {
 }
 // width of Y, the branches' input (the last shared layer, or s)
 inline int branch_ky(const Hyper& hp) { return hp.shared_dims.empty() ? hp.F : pad32(hp.shared_dims.back()); }
-// Small batches take tiles of 32 rows: with 128 rows a batch of this many
-// atoms leaves most CUs without a tile.
-constexpr int BRANCH_SMALL_ATOMS = 4096;
+// (atom, head) rows of a call.  How many blended heads a positive threshold
+// keeps is known on the device only; a quarter is what 0.01 keeps of the
+// screening model's 16.
+inline long long branch_rows(const Hyper& hp, int N, bool blend, double skip) {
+  return (long long)N * (!blend ? 1 : skip > 0.0 ? (hp.n_heads + 3) / 4 : hp.n_heads);
+}
+// Tiles of 32 rows instead of 128 while those leave CUs idle.  128 against 32
+// rows a tile (lead model, whole calls): FP32 energies 5,520 rows 981 / 958 us,
+// 8,280 1,340 / 1,347; blended 22,000 1,146 / 1,221, 88,000 1,666 / 1,999; FP64
+// 8,280 2,467 / 2,392, 13,800 3,488 / 3,376, blended 35,000 1,801 / 1,793, 65,000
+// 2,549 / 2,712; BF16 4,000 412 / 402, 13,800 819 / 827, blended 17,700 399 / 418,
+// 65,000 570 / 671.
+inline bool branch_small(int prec, const Hyper& hp, int N, bool blend, double skip) {
+  return branch_rows(hp, N, blend, skip) < (prec == PAINN_FP64 ? 32768 : 8192);
+}
 // Scratch the runtime provides for wide branches where it allocates freely.
 constexpr size_t BRANCH_SCRATCH_TARGET = (size_t)1 << 30;
 struct BranchArgs {

@@ -398,7 +398,7 @@ struct ForwardSpace {
 };
 
 static ForwardSpace forward_space(int prec, const Hyper& hp, int N, long long E, int kcols, int B, bool blend,
-                                  bool grad) {
+                                  double skip, bool grad) {
   const size_t eb = elem_bytes(prec), ab = acc_bytes(prec);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t n = (size_t)N, ne = (size_t)E, F = hp.F, H = hp.n_heads, ent = n * (blend ? H : 1);
@@ -408,7 +408,7 @@ static ForwardSpace forward_space(int prec, const Hyper& hp, int N, long long E,
   if (blend) w.head += al((size_t)B * pad32(hp.n_species) * eb) + al((size_t)B * H * ab) + al(n * H * ab);
   w.tail = w.tail_min = w.tail_full = 3 * al(n * 3 * F * eb) + al((ne + 16) * kcols * eb);
   if (branch_wide(hp)) {
-    const bool small = N < BRANCH_SMALL_ATOMS;
+    const bool small = branch_small(prec, hp, N, blend, skip);
     const size_t y = al(n * branch_row_bytes(prec, branch_ky(hp)));
     const size_t t1 = branch_tile_bytes(prec, hp.branch_dims, grad, small);
     const size_t tiles = ent / (small ? BRANCH_TM_SMALL : BRANCH_TM) + H;
@@ -852,7 +852,7 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
   }
   const LayerDev& L0 = m->prec[prec]->layers[0];
   const int kcols = L0.filt_mma.din_p > L0.filt_nb.din_p ? L0.filt_mma.din_p : L0.filt_nb.din_p;
-  const ForwardSpace sp = forward_space(prec, m->hp, g->N, g->E, kcols, g->B, blend, dy != nullptr);
+  const ForwardSpace sp = forward_space(prec, m->hp, g->N, g->E, kcols, g->B, blend, skip, dy != nullptr);
   const size_t need = sp.head + sp.tail_min;
   const size_t full = ctx->ws_tight ? need : sp.head + sp.tail_full;
   void* ws = ctx->ws;
