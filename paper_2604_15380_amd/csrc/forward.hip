@@ -1852,8 +1852,9 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
   HeadArgs ha;
   ha.N = N;
   ha.ns = (int)pm->shared.size();
-  // wide branches: this kernel runs the shared layers only
-  const bool wide_branch = pm->branch_table != nullptr;
+  // wide branches as matrix products: this kernel runs the shared layers only
+  const bool wide_branch = branch_products(P::PREC, hp, N, fa.blend, fa.skip);
+  if (wide_branch ? !pm->branch_table : !pm->head_table) return hipErrorInvalidValue;
   const bool small = branch_small(P::PREC, hp, N, fa.blend, fa.skip);
   ha.nb = wide_branch ? 0 : (int)hp.branch_dims.size();
   ha.y_out = nullptr;

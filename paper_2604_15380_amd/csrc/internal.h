@@ -141,9 +141,10 @@ struct PrecModel {      // the model cast and packed for one precision
   std::vector<std::vector<DenseDev>> branch;    // [head][layer]
   void* head_table = nullptr;                   // device [head][layer][2] = (w, b)
   // wide branches (a hidden branch layer at least BRANCH_WIDE wide) are packed
-  // for the matrix products of branch.hip instead: device table of pointers
+  // for the matrix products of branch.hip: device table of pointers
   // [head][branch layer][4] = (w, bias, w^T, plain weights of the 1-wide
   // output layer); branch_stride = 4 branch layers.  Null: narrow branches.
+  // (head_table is null where no call takes k_heads for them: FP64, FP32.)
   void* branch_table = nullptr;
   int branch_stride = 0;
   std::vector<void*> branch_ptrs;               // the table's host copy
@@ -367,15 +368,16 @@ struct BackwardArgs {
 };
 
 // ---- wide branch layers (branch.hip) --------------------------------------
-// Branches with a hidden layer this wide run as matrix products over tiles of
-// 128 rows; narrower ones (the single-head workloads' 32 to 128) stay in one
-// kernel per tile, whose weights are read from L2 cheaply.
+// Branches with a hidden layer this wide can run as matrix products over tiles
+// of rows; narrower ones (the single-head workloads' 32 to 128) stay in one
+// kernel per tile (k_heads), whose weights are read from L2 cheaply.
 constexpr int BRANCH_WIDE = 256;
-inline bool branch_wide(const Hyper& hp) {
+inline int branch_widest(const Hyper& hp) {
   int w = 0;
   for (size_t m = 0; m + 1 < hp.branch_dims.size(); ++m) w = w > hp.branch_dims[m] ? w : hp.branch_dims[m];
-  return w >= BRANCH_WIDE;
+  return w;
 }
+inline bool branch_wide(const Hyper& hp) { return branch_widest(hp) >= BRANCH_WIDE; }
 // width of Y, the branches' input (the last shared layer, or s)
 inline int branch_ky(const Hyper& hp) { return hp.shared_dims.empty() ? hp.F : pad32(hp.shared_dims.back()); }
 // (atom, head) rows of a call.  How many blended heads a positive threshold
@@ -384,12 +386,29 @@ inline int branch_ky(const Hyper& hp) { return hp.shared_dims.empty() ? hp.F : p
 inline long long branch_rows(const Hyper& hp, int N, bool blend, double skip) {
   return (long long)N * (!blend ? 1 : skip > 0.0 ? (hp.n_heads + 3) / 4 : hp.n_heads);
 }
+// Which calls of a model with wide branches run them as matrix products.  FP64
+// and FP32 always: with forces they are up to 3.0 times as fast (776, 776 wide)
+// and never slower from 256 wide on, and a forces call's energies are those of
+// an energies call bit for bit, so both take the same form.  In BF16, which has
+// no forces, k_heads' one launch without passes over Y and the hidden layers
+// often wins (whole calls, k_heads / products, F = 128, 8 heads unless said):
+//  one head per atom, from 4,096 atoms on always (12,288 atoms: 776, 776 wide
+//  427 / 451 us, 256 wide 393 / 408; lead model, 13,800 atoms 794 / 819); below
+//  up to 511 wide (1,536 atoms: 256 wide 243 / 250, but 776 wide 235 / 230, 776,
+//  776 292 / 282);
+//  blended, below 16,384 rows (1,536 atoms: 776, 776 308 / 336, 256 264 / 266;
+//  above, 12,288 atoms: 689 / 645 and 466 / 439).
+inline bool branch_products(int prec, const Hyper& hp, int N, bool blend, double skip) {
+  if (!branch_wide(hp)) return false;
+  if (prec != PAINN_BF16) return true;
+  if (blend) return branch_rows(hp, N, blend, skip) >= 16384;
+  return N < 4096 && branch_widest(hp) >= 512;
+}
 // Tiles of 32 rows instead of 128 while those leave CUs idle.  128 against 32
 // rows a tile (lead model, whole calls): FP32 energies 5,520 rows 981 / 958 us,
 // 8,280 1,340 / 1,347; blended 22,000 1,146 / 1,221, 88,000 1,666 / 1,999; FP64
 // 8,280 2,467 / 2,392, 13,800 3,488 / 3,376, blended 35,000 1,801 / 1,793, 65,000
-// 2,549 / 2,712; BF16 4,000 412 / 402, 13,800 819 / 827, blended 17,700 399 / 418,
-// 65,000 570 / 671.
+// 2,549 / 2,712; BF16 4,000 412 / 402, blended 17,700 399 / 418, 65,000 570 / 671.
 inline bool branch_small(int prec, const Hyper& hp, int N, bool blend, double skip) {
   return branch_rows(hp, N, blend, skip) < (prec == PAINN_FP64 ? 32768 : 8192);
 }

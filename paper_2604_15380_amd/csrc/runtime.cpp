@@ -305,11 +305,13 @@ painn_status build_prec(painn_model* m, int prec, PrecModel** out) {
     din = hp.shared_dims[mm];
     idx += 2;
   }
-  const bool wide_branch = branch_wide(hp);
-  if (wide_branch && e == hipSuccess) e = build_branch_table(m, pm, false);
+  // the forms that some call of the model takes (BF16: branch_products)
+  const bool fused = !branch_wide(hp) || prec == PAINN_BF16;
+  const bool products = branch_wide(hp) && (prec != PAINN_BF16 || hp.has_blend || branch_widest(hp) >= 512);
+  if (products && e == hipSuccess) e = build_branch_table(m, pm, false);
   pm->branch.resize(hp.n_heads);
   for (int h = 0; h < hp.n_heads && e == hipSuccess; ++h) {
-    if (wide_branch) {
+    if (!fused) {
       idx += 2 * hp.branch_dims.size();
       continue;
     }
@@ -322,7 +324,7 @@ painn_status build_prec(painn_model* m, int prec, PrecModel** out) {
       idx += 2;
     }
   }
-  if (e == hipSuccess && !wide_branch) {
+  if (e == hipSuccess && fused) {
     const size_t nb = hp.branch_dims.size();
     std::vector<unsigned char> tab((size_t)hp.n_heads * nb * 2 * sizeof(void*));
     void** tp = (void**)tab.data();
@@ -407,7 +409,7 @@ static ForwardSpace forward_space(int prec, const Hyper& hp, int N, long long E,
            al(MSG64_IMAGE_BYTES);
   if (blend) w.head += al((size_t)B * pad32(hp.n_species) * eb) + al((size_t)B * H * ab) + al(n * H * ab);
   w.tail = w.tail_min = w.tail_full = 3 * al(n * 3 * F * eb) + al((ne + 16) * kcols * eb);
-  if (branch_wide(hp)) {
+  if (branch_products(prec, hp, N, blend, skip)) {
     const bool small = branch_small(prec, hp, N, blend, skip);
     const size_t y = al(n * branch_row_bytes(prec, branch_ky(hp)));
     const size_t t1 = branch_tile_bytes(prec, hp.branch_dims, grad, small);

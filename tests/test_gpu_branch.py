@@ -2,7 +2,7 @@
 oracle: energies, forces and blended forces of models whose hidden branch
 layers are at least 256 wide, at the edges of the dispatch: one to three
 hidden layers, widths that pad to 128- and 160-feature workgroups, with and
-without shared layers, batches on both sides of the tile-size rule, heads
+without shared layers, batches on both sides of 4,096 atoms, heads
 without atoms and tiles with one row.  Tolerances as in the other forward and
 forces tests (the FP32 products run over three exact bf16 planes per operand,
 so their error is that of FP32 sums).  The entry point with fixed scratch runs

@@ -1,5 +1,5 @@
-"""Which tiles run wide branches (csrc/internal.h:
-branch_small): calls next to each line against the oracle, in
+"""Which tiles, and in BF16 which kernels, run wide branches (csrc/internal.h:
+branch_small, branch_products): calls next to each line against the oracle, in
 every precision, with dataset heads and blended.  Blended energies are compared
 with the oracle's head energies under the GPU's own head weights, so that the
 router's rounding (bounded in tests/test_gpu_blend.py) plays no part; the
@@ -19,8 +19,9 @@ def some(b):
     return sorted({0, b.n_struct - 1} | set(np.random.default_rng(5).choice(b.n_struct, min(4, b.n_struct)).tolist()))
 
 
-# rows = atoms: 128-row tiles from 8,192 rows on (FP64: 32,768)
-@pytest.mark.parametrize("precision,atoms", [("fp32", 8191), ("fp32", 8192), ("bf16", 8191), ("bf16", 8192),
+# rows = atoms: 128-row tiles from 8,192 rows on (FP64: 32,768), one kernel per
+# tile of atoms from 4,096 on (BF16)
+@pytest.mark.parametrize("precision,atoms", [("fp32", 8191), ("fp32", 8192), ("bf16", 4095), ("bf16", 4096),
                                              ("fp64", 8192), ("fp64", 32767), ("fp64", 32768)])
 def test_dataset_heads(rt, precision, atoms):  # noqa: F811
     print(f"branch forms, dataset heads, {precision} {atoms} atoms", flush=True)
@@ -37,7 +38,8 @@ def test_dataset_heads(rt, precision, atoms):  # noqa: F811
     m.free()
 
 
-# rows = atoms x heads, a quarter of the heads with a threshold
+# rows = atoms x heads, a quarter of the heads with a threshold; BF16: one
+# kernel per tile below 16,384
 @pytest.mark.parametrize("precision,atoms,skip", [
     ("fp32", 511, 0.0), ("fp32", 512, 0.0), ("fp32", 2047, 0.02), ("fp32", 2048, 0.02),
     ("fp64", 2047, 0.0), ("fp64", 2048, 0.0), ("bf16", 511, 0.0), ("bf16", 512, 0.0), ("bf16", 1023, 0.0),
