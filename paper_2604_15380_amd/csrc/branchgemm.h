@@ -10,8 +10,11 @@
 //   FP32: three planes of bf16, KB = 32.  x = hi + mid + lo with hi = x and
 //     mid = x - hi rounded to bf16, lo = x - hi - mid: every difference is
 //     exact and the three 8-bit significands cover the 24 bits, so the planes
-//     hold x exactly (down to the smallest exponents, where the lowest bits
-//     fall below the subnormal range).  Rounded, not cut off: with cut-off
+//     hold x exactly from 2^-110 up; below, to 2^-133, the smallest bf16
+//     subnormal (the matrix cores keep subnormals).  A product with a value
+//     below 2^-110 is so off by at most 2^-133 times the other operand.  An
+//     infinity or NaN is in the lo plane alone and acts as in FP32; two
+//     infinities that meet give NaN.  Rounded, not cut off: with cut-off
 //     planes mid and lo have the sign of x, and the products that branch.hip
 //     leaves out (mid lo, lo mid, lo lo) shrank every sum by 6e-8 of itself
 //     per layer, which the energies' sums over atoms do not average away;

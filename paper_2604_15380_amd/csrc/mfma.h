@@ -40,8 +40,11 @@ __device__ __forceinline__ bf16_t f_to_bf16(float f) {
 }
 
 // The three bf16 planes of an FP32 value (upper 16 bits each), hi and mid
-// rounded to nearest so that what is left has either sign.  A NaN keeps
-// its hi plane (quiet), an infinity too; their lower planes are zero.
+// rounded to nearest so that what is left has either sign.  A NaN (quiet) or
+// an infinity stands in the lo plane alone, which meets the other operand's hi
+// plane only: a product with a finite value is what FP32 gives.  (In the hi
+// plane an infinity met the other operand's mid and lo planes too, which are 0
+// or of the other sign: NaN.)
 __device__ __forceinline__ void split3(float x, uint32_t* p) {
   const uint32_t u = __float_as_uint(x);
   const bool fin = (u & 0x7f800000u) != 0x7f800000u;
@@ -50,9 +53,10 @@ __device__ __forceinline__ void split3(float x, uint32_t* p) {
   const float r1 = x - __uint_as_float(h);
   const uint32_t m = (__float_as_uint(r1) + 0x8000u) & 0xffff0000u;
   const float r2 = r1 - __uint_as_float(m);
-  p[0] = fin ? h : (h | ((u & 0x007fffffu) ? 0x00400000u : 0u));
+  p[0] = fin ? h : 0u;
   p[1] = fin ? m : 0u;
-  p[2] = fin ? __float_as_uint(r2) & 0xffff0000u : 0u;
+  p[2] = fin ? __float_as_uint(r2) & 0xffff0000u
+             : (u & 0xffff0000u) | ((u & 0x007fffffu) ? 0x00400000u : 0u);
 }
 
 struct P64 {

@@ -159,9 +159,10 @@ hipError_t pack_branch(PrecModel* pm, int prec, const double* W, int dout, int d
           if (prec == PAINN_FP64) {
             memcpy(&wh[blk * 1024 + (size_t)l * 16 + e * 8], &x, 8);
           } else if (prec == PAINN_FP32) {
-            // the three exact planes of the FP32 weight (as split3)
+            // the three exact planes of the FP32 weight (as split3; an
+            // infinity, from an FP64 weight past FP32's range, in the lo plane)
             float r = (float)x;
-            for (int p = 0; p < 3; ++p) {
+            for (int p = std::isfinite(r) ? 0 : 2; p < 3; ++p) {
               uint32_t u;
               memcpy(&u, &r, 4);
               if ((u & 0x7fffffffu) < 0x7f7f8000u) u += 0x8000u;
