@@ -39,7 +39,7 @@ def test_infinite_activation(rt, atoms):  # noqa: F811
     z = BIAS + SCALE * s[:, 0].cpu().numpy()
     assert np.all(np.abs(z / FLT_MAX - 1) > 1e-6)     # no atom next to the edge
     over = np.add.reduceat((z > FLT_MAX).astype(int), b.struct_ptr[:-1]) > 0
-    assert over.sum() >= 3 and (~over).sum() >= 5     # both kinds are there
+    assert over.sum() >= 2 and (~over).sum() >= 5     # both kinds are there
     E = rt.forward(m, g, "fp32").cpu().numpy()
     assert np.all(np.isposinf(E[over]))
     idx = np.nonzero(~over)[0][:6].tolist()
