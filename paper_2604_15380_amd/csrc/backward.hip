@@ -322,36 +322,10 @@ struct HeadBwdArgs {
   void* gs;                      // out: dE/ds [N][F]
   void* gh;                      // blended heads: out dE_h/ds [N][H][F] instead
   int H;
-  // wide branches: only the shared layers run here (nb = 0), from dE/dY; with
-  // blended heads the sum over an atom's kept heads of w dE_h/dY is formed
-  // first (the shared layers are the same for every head)
-  const void* dy;                // [N][ky], blended [N][H][ky]
+  // wide branches: only the shared layers run here (nb = 0), from dE/dY
+  const void* dy;                // [N][ky], or null
   int ky;
-  const void* hw;                // blended: head weights [B][H], else null
-  double skip;
-  const int32_t* atom_struct;
 };
-
-// dE/dY of atom i, column c.
-template <class A>
-__device__ __forceinline__ A dy_at(const HeadBwdArgs& a, size_t i, int c) {
-  const A* dy = (const A*)a.dy;
-  if (!a.hw) return dy[i * a.ky + c];
-  const A* w = (const A*)a.hw + (size_t)a.atom_struct[i] * a.H;
-  const A skip = (A)a.skip;
-  A y = 0;
-  for (int h = 0; h < a.H; ++h)
-    if (w[h] >= skip) y += w[h] * dy[(i * a.H + h) * a.ky + c];
-  return y;
-}
-
-// no shared layers: dE/ds = dE/dY (ky = F)
-template <class A>
-__global__ void __launch_bounds__(256) k_dy_sum(HeadBwdArgs a) {
-  const size_t tot = (size_t)a.N * a.ky;
-  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < tot; x += (size_t)gridDim.x * blockDim.x)
-    ((A*)a.gs)[x] = dy_at<A>(a, x / a.ky, (int)(x % a.ky));
-}
 
 template <class Q>
 __device__ __forceinline__ typename Q::A packed_w0(const DenseDev& L, int k) {
@@ -430,7 +404,8 @@ __device__ void heads_bwd_tile(const HeadBwdArgs& a, int head, const int* idx, t
       const int r = x / a.ky, c = x % a.ky;
       A dl = 0;
       if (idx[r] >= 0)
-        dl = dy_at<A>(a, idx[r], c) * dsilu<A>(scr[((size_t)blockIdx.x * TM + r) * a.sw + a.zoff[m] + c]);
+        dl = ((const A*)a.dy)[(size_t)idx[r] * a.ky + c] *
+             dsilu<A>(scr[((size_t)blockIdx.x * TM + r) * a.sw + a.zoff[m] + c]);
       Y[cur][r * a.ldw + c] = P::st(dl);
     }
   } else {
@@ -2039,11 +2014,8 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
     const bool wide_branch = pm->branch_table != nullptr;
     ha.nb = wide_branch ? 0 : (int)hp.branch_dims.size();
     if (ha.ns > 16 || ha.nb > 16 || ha.ns + ha.nb > 32) return hipErrorInvalidValue;
-    ha.dy = wide_branch ? ba.g_heads : nullptr;
+    ha.dy = wide_branch ? ba.dy : nullptr;
     ha.ky = branch_ky(hp);
-    ha.hw = ba.blend ? ba.hw : nullptr;
-    ha.skip = ba.skip;
-    ha.atom_struct = g->atom_struct;
     int wmax = F, off = 0;
     for (int m = 0; m < ha.ns; ++m) {
       ha.shared[m] = pm->shared[m];
@@ -2093,7 +2065,8 @@ hipError_t backward_impl(hipStream_t st, BackwardArgs& ba) {
       grid = grid < HB_GRID ? grid : HB_GRID;
     }
     if (hgx && (size_t)grid * 2 * 16 * ha.ldw * sizeof(T) > ba.xbuf_bytes) return hipErrorInvalidValue;
-    if (wide_branch && ha.ns == 0) k_dy_sum<A><<<grid_of((size_t)N * F, 256), 256, 0, st>>>(ha);
+    // (without shared layers the branches' dE/dY is dE/ds, in its place already)
+    if (wide_branch && ha.ns == 0) {}
     else if (hgx) k_heads_bwd<P, F, true, HB_NW_WIDE><<<grid, 64 * HB_NW_WIDE, 0, st>>>(ha);
     else if (wide) k_heads_bwd<P, F, false, HB_NW_WIDE><<<grid, 64 * HB_NW_WIDE, smem, st>>>(ha);
     else k_heads_bwd<P, F, false, HB_NW_NARROW><<<grid, 64 * HB_NW_NARROW, smem, st>>>(ha);

@@ -472,6 +472,17 @@ size_t branch_tile_bytes(int prec, const std::vector<int>& bd, bool grad, bool s
                  (size_t)(pad32(bd[nh - 1]) / 16) * ab + z) + 2048;
 }
 
+BranchPlan branch_plan(int prec, const Hyper& hp, int N, bool blend, double skip, bool grad) {
+  BranchPlan p;
+  const bool small = branch_small(prec, hp, N, blend, skip);
+  p.y_row = branch_row_bytes(prec, branch_ky(hp));
+  p.dyh_row = blend && grad ? (size_t)hp.n_heads * branch_ky(hp) * (prec == PAINN_FP64 ? 8 : 4) : 0;
+  p.tile = branch_tile_bytes(prec, hp.branch_dims, grad, small);
+  p.TM = small ? BRANCH_TM_SMALL : BRANCH_TM;
+  p.tiles = (long long)N * (blend ? hp.n_heads : 1) / p.TM + hp.n_heads;
+  return p;
+}
+
 hipError_t launch_branch(hipStream_t st, int prec, const BranchArgs& b) {
   if (prec == PAINN_FP64)
     return b.dy ? branch_impl<P64, true>(st, b) : branch_impl<P64, false>(st, b);

@@ -1809,6 +1809,23 @@ __global__ void __launch_bounds__(256) k_blend_reduce(int N, int H, A skip, cons
   e[i] = y;
 }
 
+// Blended dE/dY of n atoms: sum over the kept heads, in head order, of
+// w dE_h/dY (the shared layers are the same for every head).
+template <class A>
+__global__ void __launch_bounds__(256) k_blend_dy(int n, int H, int ky, A skip, const int32_t* __restrict__ atom_struct,
+                                                  const A* __restrict__ hw, const A* __restrict__ dyh,
+                                                  A* __restrict__ dy) {
+  const size_t tot = (size_t)n * ky;
+  for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < tot; x += (size_t)gridDim.x * blockDim.x) {
+    const size_t i = x / ky, c = x % ky;
+    const A* w = hw + (size_t)atom_struct[i] * H;
+    A y = 0;
+    for (int h = 0; h < H; ++h)
+      if (w[h] >= skip) y += w[h] * dyh[(i * H + h) * ky + c];
+    dy[x] = y;
+  }
+}
+
 template <class A>
 __global__ void __launch_bounds__(256) k_nan_rows(size_t n, A* __restrict__ p) {
   for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < n; x += (size_t)gridDim.x * blockDim.x)
@@ -1936,21 +1953,23 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
     if (bsmem > 64 * 1024) return hipErrorInvalidValue;
     if (B > 0) k_blend<P><<<(B + 15) / 16, 256, bsmem, st>>>(ba);
   }
-  if (fa.dataset_id || fa.blend) {
+  // group atoms [a0, a0 + n) by head into tiles of TMP entries
+  auto group = [&](int a0, int n, int TMP) {
     HeadPlan* plan = (HeadPlan*)fa.head_plan;
-    HeadTile* tiles = (HeadTile*)fa.head_tiles;
     const A* hw = fa.blend ? (const A*)fa.hw : nullptr;
     const A skip = (A)fa.skip;
-    const int nb256 = (N + 255) / 256;
-    const int TMP = !wide_branch ? TM : small ? BRANCH_TM_SMALL : BRANCH_TM;
+    const int nb256 = (n + 255) / 256;
+    const int32_t* as = fa.g->atom_struct + a0;
     k_head_clear<<<1, 64, 0, st>>>(plan);
-    k_head_count<A><<<nb256, 256, 0, st>>>(N, H, fa.dataset_id, hw, skip, fa.g->atom_struct, plan, (A*)fa.e);
-    k_head_plan<<<1, 64, 0, st>>>(H, TMP, plan, tiles);
-    k_head_scatter<A><<<nb256, 256, 0, st>>>(N, H, fa.dataset_id, hw, skip, fa.g->atom_struct, plan,
-                                             fa.head_order);
+    k_head_count<A><<<nb256, 256, 0, st>>>(n, H, fa.dataset_id, hw, skip, as, plan, (A*)fa.e + a0);
+    k_head_plan<<<1, 64, 0, st>>>(H, TMP, plan, (HeadTile*)fa.head_tiles);
+    k_head_scatter<A><<<nb256, 256, 0, st>>>(n, H, fa.dataset_id, hw, skip, as, plan, fa.head_order);
+  };
+  if (fa.dataset_id || fa.blend) {
+    if (!wide_branch) group(0, N, TM);
     ha.order = fa.head_order;
-    ha.tiles = tiles;
-    ha.plan = plan;
+    ha.tiles = (HeadTile*)fa.head_tiles;
+    ha.plan = (HeadPlan*)fa.head_plan;
     if (fa.blend) {
       grid = (int)(((long long)N * H + TM - 1) / TM);
       ha.eh = fa.eh;
@@ -1967,47 +1986,59 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
   for (int m = 0; m + 1 < ha.nb; ++m) hmax = hmax > hp.branch_dims[m] ? hmax : hp.branch_dims[m];
   const bool wide = hmax >= HEADS_WIDE;
   if (wide_branch) {
+    const BranchPlan bp = branch_plan(P::PREC, hp, N, fa.blend, fa.skip, fa.dy != nullptr);
+    if (fa.branch_scratch_bytes < branch_scratch_min(bp, N)) return hipErrorInvalidValue;
     BranchArgs b{};
     b.ky = branch_ky(hp);
-    const size_t ybytes = ((size_t)N * branch_row_bytes(P::PREC, b.ky) + 255) & ~(size_t)255;
-    if (ybytes > fa.branch_scratch_bytes) return hipErrorInvalidValue;
-    void* y = fa.branch_scratch;
-    if (ha.ns > 0) {
-      HeadArgs hs = ha;
-      hs.order = nullptr;
-      hs.tiles = nullptr;
-      hs.plan = nullptr;
-      hs.y_out = y;
-      hs.ky = b.ky;
-      const int gs = (N + TM - 1) / TM;
-      if (RT == 4) e = launch_heads_rt<P, F, 4>(st, hs, gs, smem, wide);
-      else if (RT == 2) e = launch_heads_rt<P, F, 2>(st, hs, gs, smem, wide);
-      else e = launch_heads_rt<P, F, 1>(st, hs, gs, smem, wide);
-    } else {
-      e = launch_branch_rows(st, P::PREC, N, F, fa.s, y);
-    }
-    if (e != hipSuccess) return e;
     b.pm = pm;
     b.branch_dims = &hp.branch_dims;
-    b.N = N;
     b.H = H;
     b.small = small;
     b.tiles = ha.tiles;
     b.plan = ha.plan;
     b.order = ha.order;
-    const int TMP = b.small ? BRANCH_TM_SMALL : BRANCH_TM;
-    b.max_tiles = ha.tiles ? (long long)N * (fa.blend ? H : 1) / TMP + H : (N + TMP - 1) / TMP;
-    b.y = y;
-    b.e = fa.e;
-    b.eh = ha.eh;
-    b.dy = fa.dy;
-    b.scratch = (char*)y + ybytes;
-    b.scratch_bytes = fa.branch_scratch_bytes - ybytes;
+    b.y = fa.branch_scratch;
     // an atom of a structure with an invalid dataset id is in no tile: its
     // dE/dY is NaN, so are its forces
     if (fa.dy && fa.dataset_id && !fa.blend)
       k_nan_rows<A><<<grid_for((size_t)N * b.ky, 256), 256, 0, st>>>((size_t)N * b.ky, (A*)fa.dy);
-    e = launch_branch(st, P::PREC, b);
+    const int nr = branch_range(bp, N, fa.branch_scratch_bytes);
+    for (long long r0 = 0; r0 < N && e == hipSuccess; r0 += nr) {
+      const int a0 = (int)r0, n = N - a0 < nr ? N - a0 : nr;
+      if (ha.tiles) group(a0, n, bp.TM);
+      const T* s = (const T*)fa.s + (size_t)a0 * F;
+      if (ha.ns > 0) {
+        HeadArgs hs = ha;
+        hs.N = n;
+        hs.s = s;
+        hs.order = nullptr;
+        hs.tiles = nullptr;
+        hs.plan = nullptr;
+        hs.y_out = fa.branch_scratch;
+        hs.ky = b.ky;
+        const int gs = (n + TM - 1) / TM;
+        if (RT == 4) e = launch_heads_rt<P, F, 4>(st, hs, gs, smem, wide);
+        else if (RT == 2) e = launch_heads_rt<P, F, 2>(st, hs, gs, smem, wide);
+        else e = launch_heads_rt<P, F, 1>(st, hs, gs, smem, wide);
+      } else {
+        e = launch_branch_rows(st, P::PREC, n, F, s, fa.branch_scratch);
+      }
+      if (e != hipSuccess) return e;
+      A* dy = fa.dy ? (A*)fa.dy + (size_t)a0 * b.ky : nullptr;
+      A* dyh = (A*)((char*)fa.branch_scratch + (((size_t)n * bp.y_row + 255) & ~(size_t)255));
+      const size_t used = branch_range_bytes(bp, n);
+      b.N = n;
+      b.max_tiles = ha.tiles ? (long long)n * (fa.blend ? H : 1) / bp.TM + H : (n + bp.TM - 1) / bp.TM;
+      b.e = (A*)fa.e + a0;
+      b.eh = ha.eh ? (A*)ha.eh + (size_t)a0 * H : nullptr;
+      b.dy = dy && fa.blend ? dyh : dy;
+      b.scratch = (char*)fa.branch_scratch + used;
+      b.scratch_bytes = fa.branch_scratch_bytes - used;
+      e = launch_branch(st, P::PREC, b);
+      if (dy && fa.blend)
+        k_blend_dy<A><<<grid_for((size_t)n * b.ky, 256), 256, 0, st>>>(
+            n, H, b.ky, (A)fa.skip, fa.g->atom_struct + a0, (const A*)fa.hw, dyh, dy);
+    }
   } else if (RT == 4) e = launch_heads_rt<P, F, 4>(st, ha, grid, smem, wide);
   else if (RT == 2) e = launch_heads_rt<P, F, 2>(st, ha, grid, smem, wide);
   else e = launch_heads_rt<P, F, 1>(st, ha, grid, smem, wide);

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "branchplan.h"
 #include "painn.h"
 #include "weightfile.h"
 
@@ -273,9 +274,9 @@ struct ForwardArgs {
   void* comp;
   void* hw;
   void* eh;
-  // wide branches: scratch for Y and the branch layers' activations (it shares
-  // the space of v, h and the basis rows, which the heads do not read), and,
-  // with forces, dE/dY per atom or (atom, head) [.][ky] (accumulation type)
+  // wide branches: scratch for Y, the branch layers' activations and, blended
+  // with forces, dE_h/dY (it shares the space of v, h and the basis rows, which
+  // the heads do not read); and, with forces, dE/dY [N][ky] (accumulation type)
   void* branch_scratch;
   size_t branch_scratch_bytes;
   void* dy;
@@ -363,7 +364,8 @@ struct BackwardArgs {
   bool blend;
   double skip;
   const void* hw;
-  void* g_heads;            // wide branches: dE/dY, else (blended) dE_h/ds per (atom, head)
+  void* g_heads;            // blended narrow branches: dE_h/ds per (atom, head)
+  const void* dy;           // wide branches: the forward's dE/dY [N][ky]
   Profiler* prof;
 };
 
@@ -412,8 +414,7 @@ inline bool branch_products(int prec, const Hyper& hp, int N, bool blend, double
 inline bool branch_small(int prec, const Hyper& hp, int N, bool blend, double skip) {
   return branch_rows(hp, N, blend, skip) < (prec == PAINN_FP64 ? 32768 : 8192);
 }
-// Scratch the runtime provides for wide branches where it allocates freely.
-constexpr size_t BRANCH_SCRATCH_TARGET = (size_t)1 << 30;
+BranchPlan branch_plan(int prec, const Hyper& hp, int N, bool blend, double skip, bool grad);
 struct BranchArgs {
   const PrecModel* pm;
   const std::vector<int>* branch_dims;

@@ -396,8 +396,8 @@ static size_t head_tiles_bytes(size_t entries) { return (entries / 16 + 65) * 16
 
 struct ForwardSpace {
   size_t head, tail;     // bytes before and in the buffers that end with the layers
-  size_t tail_min;       // the tail wide branches cannot do without (Y and one tile)
-  size_t tail_full;      // the tail that takes all their tiles, or BRANCH_SCRATCH_TARGET, at once
+  size_t tail_min;       // the tail wide branches cannot do without (a tile's atoms and one tile)
+  size_t tail_full;      // the tail that takes them at once, as far as BRANCH_SCRATCH_TARGET goes
 };
 
 static ForwardSpace forward_space(int prec, const Hyper& hp, int N, long long E, int kcols, int B, bool blend,
@@ -411,15 +411,10 @@ static ForwardSpace forward_space(int prec, const Hyper& hp, int N, long long E,
   if (blend) w.head += al((size_t)B * pad32(hp.n_species) * eb) + al((size_t)B * H * ab) + al(n * H * ab);
   w.tail = w.tail_min = w.tail_full = 3 * al(n * 3 * F * eb) + al((ne + 16) * kcols * eb);
   if (branch_products(prec, hp, N, blend, skip)) {
-    const bool small = branch_small(prec, hp, N, blend, skip);
-    const size_t y = al(n * branch_row_bytes(prec, branch_ky(hp)));
-    const size_t t1 = branch_tile_bytes(prec, hp.branch_dims, grad, small);
-    const size_t tiles = ent / (small ? BRANCH_TM_SMALL : BRANCH_TM) + H;
-    size_t all = tiles * t1;
-    if (all > BRANCH_SCRATCH_TARGET) all = BRANCH_SCRATCH_TARGET;
-    if (all < t1) all = t1;
-    if (w.tail_min < y + t1) w.tail_min = y + t1;
-    if (w.tail_full < y + all) w.tail_full = y + all;
+    const BranchPlan p = branch_plan(prec, hp, N, blend, skip, grad);
+    const size_t least = branch_scratch_min(p, N), full = branch_scratch_full(p, N);
+    if (w.tail_min < least) w.tail_min = least;
+    if (w.tail_full < full) w.tail_full = full;
   }
   return w;
 }
@@ -976,17 +971,28 @@ static size_t forces_scratch_rows(int N) {
   return (size_t)N > (size_t)HB_GRID * 16 ? (size_t)N : (size_t)HB_GRID * 16;
 }
 
-// dE/dY per atom or (atom, head) with wide branches; else, blended, dE_h/ds.
+// dE_h/ds of blended narrow branches.
 static size_t forces_gheads_bytes(int prec, const Hyper& hp, int N, bool blend) {
-  const size_t rows = (size_t)N * (blend ? hp.n_heads : 1) * acc_bytes(prec);
-  return branch_wide(hp) ? rows * branch_ky(hp) : blend ? rows * hp.F : 0;
+  return blend && !branch_wide(hp) ? (size_t)N * hp.n_heads * hp.F * acc_bytes(prec) : 0;
+}
+
+// g_s, g_v after a layer's message and g_h, whose space holds wide branches'
+// dE/dY until the shared layers' reverse pass has read it (which is before the
+// layers write it).
+static size_t forces_after_bytes(int prec, const Hyper& hp, int N) {
+  const size_t ab = acc_bytes(prec), n = (size_t)N;
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t g = al(n * hp.F * ab) + 2 * al(n * 3 * hp.F * ab);
+  const size_t dy = branch_wide(hp) ? al(n * branch_ky(hp) * ab) : 0;
+  return g > dy ? g : dy;
 }
 
 static size_t forces_workspace_bytes(int prec, const Hyper& hp, int N, long long E, int kcols, bool blend) {
   const size_t eb = elem_bytes(prec), ab = acc_bytes(prec), n = (size_t)N, F = hp.F;
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return al(forces_xbuf_bytes(prec, hp, N, blend)) + al(forces_gheads_bytes(prec, hp, N, blend)) +
-         al(SaveLayout::bytes(n, F, hp.L, eb)) + 2 * al(n * F * ab) + 3 * al(n * 3 * F * ab) +
+         al(SaveLayout::bytes(n, F, hp.L, eb)) + al(n * F * ab) + al(n * 3 * F * ab) +
+         forces_after_bytes(prec, hp, N) +
          2 * al(((size_t)E + 16) * kcols * eb) + al((size_t)E * 4 * ab) + al((size_t)E * (F / 16) * 4 * ab) +
          al(forces_scratch_rows(N) * forces_scratch_width(hp) * ab) + al((size_t)E * 3 * sizeof(double));
 }
@@ -1131,10 +1137,14 @@ static painn_status forces_impl(painn_ctx* ctx, const painn_model* model, const 
   b.g_heads = p; p += al(forces_gheads_bytes(precision, hp, g->N, blend));
   b.save = p; p += al(SaveLayout::bytes(N, F, hp.L, eb));
   b.gs = p; p += al(N * F * ab);
-  b.gs2 = p; p += al(N * F * ab);
   b.gv = p; p += al(N * 3 * F * ab);
-  b.gv2 = p; p += al(N * 3 * F * ab);
-  b.gh = p; p += al(N * 3 * F * ab);
+  b.gs2 = p;
+  b.gv2 = p + al(N * F * ab);
+  b.gh = p + al(N * F * ab) + al(N * 3 * F * ab);
+  // (without shared layers dE/dY is dE/ds)
+  void* dy = !branch_wide(hp) ? nullptr : hp.shared_dims.empty() ? b.gs : (void*)p;
+  b.dy = dy;
+  p += forces_after_bytes(precision, hp, g->N);
   b.dbasis = p; p += al(((size_t)g->E + 16) * kcols * eb);
   b.basis_t = p; p += al(((size_t)g->E + 16) * kcols * eb);
   b.einfo_t = p; p += al((size_t)g->E * 4 * ab);
@@ -1144,7 +1154,7 @@ static painn_status forces_impl(painn_ctx* ctx, const painn_model* model, const 
   b.gr = (double*)p;
   ForwardArgs fa{};
   painn_status st = run_forward(ctx, model, graph, dataset_id, precision, hp.L - 1, energies, nullptr, nullptr,
-                                blend, skip, weights, b.save, &fa, nullptr, 0, branch_wide(hp) ? b.g_heads : nullptr);
+                                blend, skip, weights, b.save, &fa, nullptr, 0, dy);
   if (st != PAINN_OK) return st;
   b.m = m;
   b.pm = pm;
