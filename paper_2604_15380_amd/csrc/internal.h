@@ -10,6 +10,7 @@
 #include "branchplan.h"
 #include "painn.h"
 #include "weightfile.h"
+#include "workspace.h"
 
 typedef uint16_t bf16_t;  // bfloat16 storage (upper half of an IEEE float)
 
@@ -178,12 +179,9 @@ struct painn_ctx {
   std::string err;
   DevStatus* h_status = nullptr;   // pinned host mirror of the graph status
   // forward workspace (grown on demand)
-  void* ws = nullptr;
-  size_t ws_bytes = 0;
-  bool ws_tight = false;   // a workspace with the full branch scratch did not fit
+  Workspace ws;
   // reverse-pass workspace (saved activations and gradients; grown on demand)
-  void* bws = nullptr;
-  size_t bws_bytes = 0;
+  Workspace bws;
 };
 
 struct painn_model {

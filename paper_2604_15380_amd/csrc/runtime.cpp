@@ -534,8 +534,8 @@ painn_status painn_destroy(painn_ctx* ctx) {
   if (!ctx) return PAINN_OK;
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
-  if (ctx->ws) (void)hipFree(ctx->ws);
-  if (ctx->bws) (void)hipFree(ctx->bws);
+  if (ctx->ws.p) (void)hipFree(ctx->ws.p);
+  if (ctx->bws.p) (void)hipFree(ctx->bws.p);
   if (ctx->h_status) (void)hipHostFree(ctx->h_status);
   prof_free(ctx->prof);
   delete ctx;
@@ -820,6 +820,32 @@ painn_status painn_graph_csr(const painn_graph* g, int64_t* n_edges, int32_t* n_
   return PAINN_OK;
 }
 
+// Whether the context's stream is being captured (or may not be asked now,
+// because another one is).
+static bool capturing(painn_ctx* ctx) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+static void release_workspace(painn_ctx* ctx, void* p) {
+  (void)hipStreamSynchronize(ctx->stream);
+  (void)hipFree(p);
+}
+
+static bool grow_workspace(painn_ctx* ctx, Workspace& w, size_t need, size_t full, int slack) {
+  return workspace_grow(
+      w, need, full, slack, [&] { return capturing(ctx); },
+      [&](size_t n) {
+        void* p = nullptr;
+        if (hipMalloc(&p, n) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return (void*)nullptr;
+      },
+      [&](void* p) { release_workspace(ctx, p); });
+}
+
 static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const painn_graph* g,
                                 const int32_t* dataset_id, painn_precision prec, int stop_layer,
                                 double* energies, double* s_out, double* v_out, bool blend = false,
@@ -852,37 +878,19 @@ static painn_status run_forward(painn_ctx* ctx, const painn_model* model, const 
   const int kcols = L0.filt_mma.din_p > L0.filt_nb.din_p ? L0.filt_mma.din_p : L0.filt_nb.din_p;
   const ForwardSpace sp = forward_space(prec, m->hp, g->N, g->E, kcols, g->B, blend, skip, dy != nullptr);
   const size_t need = sp.head + sp.tail_min;
-  const size_t full = ctx->ws_tight ? need : sp.head + sp.tail_full;
-  void* ws = ctx->ws;
+  void* ws = ws_fixed;
   size_t ws_total = ws_fixed_bytes;
   if (ws_fixed) {
     if (need > ws_fixed_bytes)
       return fail(ctx, PAINN_E_ARG, "this batch needs " + std::to_string(need) +
                                         " bytes of workspace; painn_forward_noalloc has " +
                                         std::to_string(ws_fixed_bytes));
-    ws = ws_fixed;
-  } else if (full > ctx->ws_bytes) {
-    if (ctx->ws) {
-      (void)hipStreamSynchronize(ctx->stream);
-      (void)hipFree(ctx->ws);
-      ctx->ws = nullptr;
-      ctx->ws_bytes = 0;
-    }
-    const size_t slack = need + need / 4;
-    size_t want = slack > full ? slack : full;
-    hipError_t e = hipMalloc(&ctx->ws, want);
-    if (e != hipSuccess && full > need) {
-      // without the full branch scratch the branches run in more chunks
-      (void)hipGetLastError();
-      ctx->ws_tight = true;
-      want = slack;
-      e = hipMalloc(&ctx->ws, want);
-    }
-    if (e != hipSuccess) return fail(ctx, PAINN_E_OOM, "forward workspace allocation failed");
-    ctx->ws_bytes = want;
-    ws = ctx->ws;
+  } else {
+    if (!grow_workspace(ctx, ctx->ws, need, sp.head + sp.tail_full, 4))
+      return fail(ctx, PAINN_E_OOM, "forward workspace allocation failed");
+    ws = ctx->ws.p;
+    ws_total = ctx->ws.bytes;
   }
-  if (!ws_fixed) ws_total = ctx->ws_bytes;
   ForwardArgs a{};
   a.m = m;
   a.pm = m->prec[prec];
@@ -1113,24 +1121,16 @@ static painn_status forces_impl(painn_ctx* ctx, const painn_model* model, const 
   }
   const int kcols = pm->layers[0].filt_mma.din_p;
   const size_t need = forces_workspace_bytes(precision, hp, g->N, g->E, kcols, blend);
-  if (need > ctx->bws_bytes) {
-    if (ctx->bws) {
-      (void)hipStreamSynchronize(ctx->stream);
-      (void)hipFree(ctx->bws);
-      ctx->bws = nullptr;
-      ctx->bws_bytes = 0;
-    }
-    const size_t want = need + need / 8;
-    hipError_t e = hipMalloc(&ctx->bws, want);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
+  if (!grow_workspace(ctx, ctx->bws, need, need, 8)) {
+    // the forward's workspace may hold more than it needs: give it back
+    if (ctx->ws.p) release_workspace(ctx, ctx->ws.p);
+    ctx->ws = Workspace();
+    if (!grow_workspace(ctx, ctx->bws, need, need, 8))
       return fail(ctx, PAINN_E_OOM, "reverse-pass workspace allocation failed");
-    }
-    ctx->bws_bytes = want;
   }
   const size_t N = g->N, F = hp.F, ab = acc_bytes(precision);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  char* p = (char*)ctx->bws;
+  char* p = (char*)ctx->bws.p;
   BackwardArgs b{};
   b.xbuf_bytes = forces_xbuf_bytes(precision, hp, g->N, blend);
   b.xbuf = p; p += al(b.xbuf_bytes);

@@ -1,5 +1,7 @@
-"""The host rules that cut the wide branches' scratch (csrc/branchplan.h), built
-on their own and checked over random plans."""
+"""Host rules of the workspaces, built on their own: how the wide branches'
+scratch is cut (csrc/branchplan.h), over random plans, and how a workspace
+grows (csrc/workspace.h), against a device with little memory and under
+capture."""
 import os
 import shutil
 import subprocess
@@ -9,14 +11,15 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_branch_plan(tmp_path):
+@pytest.mark.parametrize("name", ["branchplan_check", "workspace_check"])
+def test_native(tmp_path, name):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ not available")
-    out = str(tmp_path / "branchplan_check")
+    out = str(tmp_path / name)
     r = subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
                         "-I" + os.path.join(ROOT, "paper_2604_15380_amd", "csrc"),
-                        os.path.join(ROOT, "tests", "native", "branchplan_check.cpp"), "-o", out],
+                        os.path.join(ROOT, "tests", "native", name + ".cpp"), "-o", out],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     env = dict(os.environ)
