@@ -1810,19 +1810,24 @@ __global__ void __launch_bounds__(256) k_blend_reduce(int N, int H, A skip, cons
 }
 
 // Blended dE/dY of n atoms: sum over the kept heads, in head order, of
-// w dE_h/dY (the shared layers are the same for every head).
+// w dE_h/dY (the shared layers are the same for every head); four columns per
+// thread (ky is a multiple of 32).
 template <class A>
 __global__ void __launch_bounds__(256) k_blend_dy(int n, int H, int ky, A skip, const int32_t* __restrict__ atom_struct,
                                                   const A* __restrict__ hw, const A* __restrict__ dyh,
                                                   A* __restrict__ dy) {
-  const size_t tot = (size_t)n * ky;
+  const size_t tot = (size_t)n * (ky / 4);
   for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < tot; x += (size_t)gridDim.x * blockDim.x) {
-    const size_t i = x / ky, c = x % ky;
+    const size_t i = x / (ky / 4), c = 4 * (x % (ky / 4));
     const A* w = hw + (size_t)atom_struct[i] * H;
-    A y = 0;
-    for (int h = 0; h < H; ++h)
-      if (w[h] >= skip) y += w[h] * dyh[(i * H + h) * ky + c];
-    dy[x] = y;
+    Quad<A> y{};
+    for (int h = 0; h < H; ++h) {
+      const A wh = w[h];
+      if (!(wh >= skip)) continue;
+      const Quad<A> d = *(const Quad<A>*)(dyh + (i * H + h) * ky + c);
+      for (int k = 0; k < 4; ++k) y.x[k] += wh * d.x[k];
+    }
+    *(Quad<A>*)(dy + i * ky + c) = y;
   }
 }
 
@@ -2036,7 +2041,7 @@ hipError_t launch_heads(hipStream_t st, ForwardArgs& fa) {
       b.scratch_bytes = fa.branch_scratch_bytes - used;
       e = launch_branch(st, P::PREC, b);
       if (dy && fa.blend)
-        k_blend_dy<A><<<grid_for((size_t)n * b.ky, 256), 256, 0, st>>>(
+        k_blend_dy<A><<<grid_for((size_t)n * b.ky / 4, 256), 256, 0, st>>>(
             n, H, b.ky, (A)fa.skip, fa.g->atom_struct + a0, (const A*)fa.hw, dyh, dy);
     }
   } else if (RT == 4) e = launch_heads_rt<P, F, 4>(st, ha, grid, smem, wide);
