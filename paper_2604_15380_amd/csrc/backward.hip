@@ -813,7 +813,7 @@ __global__ void __launch_bounds__((64 * ub_nw<P, F>())) k_phi_bwd(PhiBwdArgs a) 
 // buffers while the accumulators stay in registers: a chunk is filled, one
 // barrier, multiplied; the next fill writes the other buffer, so a wave that
 // is done early fills while the others multiply.  FP64 at F = 384 fits the
-// LDS this way (148 KiB instead of 16 rows of 4F = 198 KiB, whose 3F-wide
+// LDS this way (144 KiB instead of 16 rows of 4F = 192 KiB, whose 3F-wide
 // part had to be read from global memory by every wave), and a wave's feature
 // tiles share each activation read.
 //
@@ -1111,14 +1111,15 @@ __device__ __forceinline__ V buf_ld8(__amdgpu_buffer_rsrc_t r, uint32_t off, int
 }
 typedef double bwd_d2 __attribute__((ext_vector_type(2)));
 
-// At 6 to 9 k-blocks a wave owns 32 channels as two feature tiles whose
-// columns interleave (column c of tile q = channel 2 c + q), so that a lane's
-// gathers of the receivers' gradients are 16-byte loads and the basis rows,
-// edge info and per-edge sums of a chunk serve twice the channels.  The
-// filter fragments of the workgroup's channels (up to 128) sit in LDS, shared
-// by two or more streams of senders.  (With one tile per wave and a filter
-// copy each: bulk reverse message 3,861 us per launch.)  With 3 k-blocks the
-// fragments fit in registers, past 9 not in the LDS: one tile per wave.
+// Up to 9 k-blocks a wave owns 32 channels as two feature tiles whose columns
+// interleave (column c of tile q = channel 2 c + q), so that a lane's gathers
+// of the receivers' gradients are 16-byte loads and the basis rows, edge info
+// and per-edge sums of a chunk serve twice the channels.  The filter fragments
+// of the workgroup's channels (up to 128) sit in LDS, shared by two or more
+// streams of senders.  (Against one tile per wave, with a filter copy each at 9
+// k-blocks and the fragments in registers at 3: bulk 3,861 -> 2,993 us per
+// launch, lead model 1,603 -> 1,053.)  Past 9 k-blocks the fragments do not fit
+// the LDS: one tile per wave, fragments from L2.
 template <int KBM>
 constexpr bool mb_pair() { return KBM <= 9; }
 template <class P, int F, int KBM>
@@ -1351,7 +1352,7 @@ k_message_bwd(MsgBwdArgs a) {
     // the loops).
     // (With the LDS copy the opaque offset keeps its reads in the loop.)
     int wofs = 0;
-    if constexpr (WIMG || FTW * 3 * KBM * (int)sizeof(A) / 4 > 40) asm volatile("" : "+s"(wofs));
+    asm volatile("" : "+s"(wofs));
     // per-edge partial sums: [dE/drhat x, y, z, dE/dd] x 4 rows
     A vals[16];
 #pragma unroll

@@ -16,15 +16,21 @@
 namespace rows {
 
 // Whether a batch of N atoms takes this form, forward or reverse, as measured
-// (whole calls, fused against this form, structures of 96 atoms).  Forward:
-// FP32 F = 384 N = 768 513 -> 380 us, 1,536 523 -> 515, 2,304 595 -> 681; F =
-// 256 1,536 1,003 -> 756; F = 128 1,536 411 -> 354; FP64 F = 256 768 1,831 ->
-// 1,540, 1,152 1,843 -> 1,787, 1,536 1,847 -> 1,931; F = 128 768 608 -> 580,
-// 1,152 616 -> 639; F = 64 (molecules) 600 282 -> 246.  In reverse the
-// element-wise operands are formed once per 16 features, so the line lies
-// lower: FP32 F = 384 96 atoms 864 -> 626 us, 384 918 -> 863, 576 948 -> 989;
-// FP64 F = 384 96 1,233 -> 954, 288 1,281 -> 1,274, 384 1,414 -> 1,514; below
-// F = 256 the fused FP64 kernels win from the start.
+// (whole calls, us, fused -> this form; energies for the forward).
+//  FP32 F = 384: 1,152 atoms 465 -> 385, 1,536 467 -> 453, 2,304 512 -> 597;
+//   F = 256: 1,536 1,656 -> 1,273, 2,304 2,131 -> 1,940; F = 128: 1,536 350 ->
+//   294, 2,304 383 -> 366; F = 64: 768 174 -> 170, 1,536 176 -> 171, 2,304 184
+//   -> 193 (from 768 on the two are within 3 %).
+//  FP64 F = 384: 1,152 738 -> 668, 1,536 740 -> 785; F = 256: 1,152 1,820 ->
+//   1,764, 1,536 1,823 -> 1,898; F = 128: 768 514 -> 488, 1,152 536 -> 551; F =
+//   64: 1,152 264 -> 236, 2,304 276 -> 268.
+// In reverse the element-wise operands are formed once per 16 features, so the
+// line lies lower (forces calls with the forward in its own form):
+//  FP32 F = 384: 96 864 -> 626, 384 918 -> 863, 576 948 -> 989.
+//  FP64 F = 384: 96 1,233 -> 954, 288 1,281 -> 1,274, 384 1,414 -> 1,514; F =
+//   256: both passes gain 820 us at 240 atoms and 415 at 384, the forward alone
+//   567 and 450; below F = 256 the fused kernels win from the start.
+// A structure's last bits depend on the form, so on the batch it is in.
 template <class P, int F>
 inline bool small_rows(int N, bool reverse) {
   if (P::PREC == PAINN_BF16) return false;
