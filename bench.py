@@ -40,7 +40,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 # the kernel sources a stored traffic measurement depends on (per mode)
 KERNEL_SOURCES = ["paper_2604_15380_amd/csrc/forward.hip", "paper_2604_15380_amd/csrc/mfma.h",
                   "paper_2604_15380_amd/csrc/neighbors.hip", "paper_2604_15380_amd/csrc/rows.h",
-                  "paper_2604_15380_amd/csrc/branch.hip", "paper_2604_15380_amd/csrc/branchgemm.h"]
+                  "paper_2604_15380_amd/csrc/branch.hip", "paper_2604_15380_amd/csrc/branchgemm.h",
+                  "paper_2604_15380_amd/csrc/internal.h"]
 KERNEL_SOURCES_FORCES = KERNEL_SOURCES + ["paper_2604_15380_amd/csrc/backward.hip"]
 
 

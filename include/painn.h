@@ -26,6 +26,9 @@
  *    synchronisation is inside painn_build_graph (it reads back the edge
  *    count) and painn_synchronize.
  *  - A context is not thread-safe; use one context per host thread.
+ *  - The same batch gives the same bits on every call.  A structure's last
+ *    bits may depend on the batch it is in: small and large batches take
+ *    different kernels, whose sums run in other orders.
  */
 #ifndef PAINN_H
 #define PAINN_H

@@ -3,7 +3,7 @@
 //
 // A row is one (atom, head) entry of the heads' grouping (k_head_*).  Per
 // branch layer one launch of k_branch runs out[row][feature] over tiles of
-// 128 rows (32 for small batches) x 128 or 160 features; activations go
+// 128 rows (32 where rows are few) x 128 or 160 features; activations go
 // between launches through a scratch in HBM in the operand layout of
 // branchgemm.h, and the launches of one chunk of tiles share that scratch.
 // With gradients the reverse products follow in the same chunk (they reuse
@@ -17,10 +17,10 @@
 // the matrix cores' peak.  With 128 rows x 160 features per workgroup each
 // byte staged in LDS feeds 128 to 160 products, and the pre-activations are
 // formed once instead of once forward and once in reverse.  FP32 products run
-// on the BF16 matrix cores over the three exact planes of each operand: the
-// six products of order 2^-16 and above of the nine (the rest are below
-// FP32's rounding), 96 cycles per 16x16x32 against 256 for the FP32
-// instruction.
+// on the BF16 matrix cores over three planes of each operand (branchgemm.h,
+// also for what they do with infinities and the smallest values): the six
+// products of order 2^-16 and above of the nine (the rest are below FP32's
+// rounding), 96 cycles per 16x16x32 against 256 for the FP32 instruction.
 #include "branchgemm.h"
 #include "mfma.h"
 
@@ -324,7 +324,7 @@ void launch_one(hipStream_t st, GemmArgs a) {
 }
 
 // Feature tiles per wave: 4 (128 features per workgroup) or 5 (160) by which
-// pads less; 2 (64) for narrow results and for small batches.
+// pads less; 2 (64) for narrow results and for tiles of 32 rows.
 template <class P, int EPI, bool FIRST, bool GRAD>
 void launch_gemm(hipStream_t st, const GemmArgs& a, bool small) {
   if (small) return launch_one<P, 2, 1, EPI, FIRST, GRAD>(st, a);

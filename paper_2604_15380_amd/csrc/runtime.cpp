@@ -391,7 +391,8 @@ painn_status parse_model(painn_ctx* ctx, const unsigned char* buf, size_t n, pai
 // and the per-head atom energies [N][H] (accumulation type).  Last the
 // buffers that nothing reads once the layers have run: v[0], v[1], h [N][3F]
 // and the radial basis rows [E + 16][kcols] (storage type); wide branches
-// take their place with Y and the branch layers' scratch.
+// take their place with Y, dE_h/dY and the branch layers' scratch
+// (branchplan.h).
 static size_t head_tiles_bytes(size_t entries) { return (entries / 16 + 65) * 16; }
 
 struct ForwardSpace {
