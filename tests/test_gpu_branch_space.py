@@ -6,7 +6,7 @@ import torch
 
 import synth
 from helpers import TOL, check_energies, check_forces
-from oracle.forces import structure_forces_blend
+from oracle.forces import structure_forces, structure_forces_blend
 from oracle.painn import batch_energies
 from test_gpu_branch import batch, rt  # noqa: F401
 
@@ -40,6 +40,27 @@ def test_fixed_scratch_wide_shared(rt, atoms):  # noqa: F811
     idx = [0, b.n_struct // 2, b.n_struct - 1]
     Er, Ar = batch_energies(b, hp, W, idx)
     check_energies(want.cpu().numpy()[idx], Er, Ar, TOL["fp32"], f"wide shared {atoms}")
+    g.free()
+    m.free()
+
+
+def test_forces_wide_shared(rt):  # noqa: F811
+    """dE/dY wider than the gradients whose space it takes (1,024 against
+    7 F = 448 columns), dataset heads and blended, FP32."""
+    print("forces, 1,024-wide shared layer", flush=True)
+    hp, W, m = wide_shared(rt, 5)
+    b = batch(301, hp.n_heads)
+    g = rt.build_graph(rt.upload_batch(b), hp.cutoff)
+    ds = torch.as_tensor(b.dataset_id, dtype=torch.int32, device=rt.device)
+    idx = list(range(b.n_struct))
+    E, F = rt.forces(m, g, "fp32", dataset_id=ds)
+    assert torch.equal(E, rt.forward(m, g, "fp32", dataset_id=ds))
+    ref = [structure_forces(*b.structure(k), hp, W)["F"] for k in idx]
+    check_forces(F.cpu().numpy(), b, ref, idx, 2e-5, "wide shared, dataset heads")
+    E, F = rt.forces_blend(m, g, "fp32", skip=0.0)
+    assert torch.equal(E, rt.forward_blend(m, g, "fp32", skip=0.0))
+    ref = [structure_forces_blend(*b.structure(k)[:4], hp, W, skip=0.0)["F"] for k in idx]
+    check_forces(F.cpu().numpy(), b, ref, idx, 2e-5, "wide shared, blended")
     g.free()
     m.free()
 
