@@ -142,47 +142,64 @@ hipError_t pack_dense(PrecModel* pm, int prec, const double* W, const double* b,
   return upload(pm, bh, &out->b);
 }
 
-// Pack W [dout][din] for the branch products (branchgemm.h); tr: its transpose.
+// The three bf16 planes of an FP32 weight, as split3 forms them (an infinity,
+// from an FP64 weight past FP32's range, in the lo plane).
+inline void split3_host(float x, uint16_t* hi, uint16_t* mid, uint16_t* lo) {
+  uint32_t u;
+  memcpy(&u, &x, 4);
+  if ((u & 0x7f800000u) == 0x7f800000u) {
+    *hi = *mid = 0;
+    *lo = (uint16_t)(u >> 16);
+    return;
+  }
+  float f;
+  const uint32_t h = ((u & 0x7fffffffu) < 0x7f7f8000u ? u + 0x8000u : u) & 0xffff0000u;
+  memcpy(&f, &h, 4);
+  const float r1 = x - f;
+  uint32_t m;
+  memcpy(&m, &r1, 4);
+  m = (m + 0x8000u) & 0xffff0000u;
+  memcpy(&f, &m, 4);
+  const float r2 = r1 - f;
+  uint32_t l;
+  memcpy(&l, &r2, 4);
+  *hi = (uint16_t)(h >> 16);
+  *mid = (uint16_t)(m >> 16);
+  *lo = (uint16_t)(l >> 16);
+}
+
+// Pack W [dout][din] for the branch products in FP64 or FP32 (branchgemm.h;
+// BF16's form is pack_dense's); tr: its transpose.
 hipError_t pack_branch(PrecModel* pm, int prec, const double* W, int dout, int din, bool tr, void** out) {
   const int KB = branch_kb(prec), NP = branch_planes(prec), KPL = KB / 4;
   const int no = tr ? din : dout, ni = tr ? dout : din;
   const int nft = pad32(no) / 16, nkb = pad32(ni) / KB;
+  const size_t so = tr ? 1 : (size_t)din, sk = tr ? (size_t)din : 1;
   std::vector<unsigned char> wh(branch_pack_bytes(prec, no, ni), 0);
   for (int ft = 0; ft < nft; ++ft)
-    for (int kb = 0; kb < nkb; ++kb)
-      for (int l = 0; l < 64; ++l)
-        for (int e = 0; e < KPL; ++e) {
-          const int o = 16 * ft + branch_feature(prec, l % 16), k = KB * kb + KPL * (l / 16) + e;
-          if (o >= no || k >= ni) continue;
-          const double x = tr ? W[(size_t)k * din + o] : W[(size_t)o * din + k];
-          const size_t blk = ((size_t)ft * nkb + kb) * NP;
-          if (prec == PAINN_FP64) {
-            memcpy(&wh[blk * 1024 + (size_t)l * 16 + e * 8], &x, 8);
-          } else if (prec == PAINN_FP32) {
-            // the three exact planes of the FP32 weight (as split3; an
-            // infinity, from an FP64 weight past FP32's range, in the lo plane)
-            float r = (float)x;
-            for (int p = std::isfinite(r) ? 0 : 2; p < 3; ++p) {
-              uint32_t u;
-              memcpy(&u, &r, 4);
-              if ((u & 0x7fffffffu) < 0x7f7f8000u) u += 0x8000u;
-              u &= 0xffff0000u;
-              const uint16_t hi = (uint16_t)(u >> 16);
-              memcpy(&wh[(blk + p) * 1024 + (size_t)l * 16 + e * 2], &hi, 2);
-              float f;
-              memcpy(&f, &u, 4);
-              r = std::isfinite(r) ? r - f : 0.0f;
-            }
-          } else {
-            const bf16_t h = to_bf16(x);
-            memcpy(&wh[blk * 1024 + (size_t)l * 16 + e * 2], &h, 2);
-          }
+    for (int kb = 0; kb < nkb; ++kb) {
+      unsigned char* blk = wh.data() + ((size_t)ft * nkb + kb) * NP * 1024;
+      for (int l = 0; l < 64; ++l) {
+        const int o = 16 * ft + branch_feature(prec, l % 16), k0 = KB * kb + KPL * (l / 16);
+        if (o >= no) continue;
+        const int ne = ni - k0 < KPL ? ni - k0 : KPL;
+        const double* src = W + o * so + k0 * sk;
+        if (prec == PAINN_FP64) {
+          double* d = (double*)(blk + l * 16);
+          for (int e = 0; e < ne; ++e) d[e] = src[e * sk];
+        } else {
+          uint16_t* d = (uint16_t*)(blk + l * 16);
+          for (int e = 0; e < ne; ++e) split3_host((float)src[e * sk], d + e, d + 512 + e, d + 1024 + e);
         }
+      }
+    }
   return upload(pm, wh, out);
 }
 
 // The pointer table of the wide branches: [head][layer][4] = (w, bias, w^T,
-// plain row 0).  `with_T` adds the transposed hidden layers (forces).
+// plain row 0).  `with_T` adds the transposed hidden layers (forces).  BF16:
+// weights and biases are those packed for k_heads, whose operand order is the
+// same.
 hipError_t build_branch_table(const painn_model* m, PrecModel* pm, bool with_T) {
   const Hyper& hp = m->hp;
   const int prec = pm->prec, nb = (int)hp.branch_dims.size();
@@ -200,6 +217,10 @@ hipError_t build_branch_table(const painn_model* m, PrecModel* pm, bool with_T) 
       const int dout = hp.branch_dims[mm];
       void** slot = &pm->branch_ptrs[((size_t)h * nb + mm) * 4];
       const bool hidden = mm + 1 < nb;
+      if (prec == PAINN_BF16) {
+        slot[0] = hidden ? pm->branch[h][mm].w : nullptr;
+        slot[1] = pm->branch[h][mm].b;
+      }
       if (hidden && !slot[0]) e = pack_branch(pm, prec, W, dout, di, false, &slot[0]);
       if (e == hipSuccess && !slot[1]) {
         std::vector<unsigned char> bh((size_t)pad32(dout) * acc_bytes(prec), 0);
@@ -309,7 +330,6 @@ painn_status build_prec(painn_model* m, int prec, PrecModel** out) {
   // the forms that some call of the model takes (BF16: branch_products)
   const bool fused = !branch_wide(hp) || prec == PAINN_BF16;
   const bool products = branch_wide(hp) && (prec != PAINN_BF16 || hp.has_blend || branch_widest(hp) >= 512);
-  if (products && e == hipSuccess) e = build_branch_table(m, pm, false);
   pm->branch.resize(hp.n_heads);
   for (int h = 0; h < hp.n_heads && e == hipSuccess; ++h) {
     if (!fused) {
@@ -336,6 +356,7 @@ painn_status build_prec(painn_model* m, int prec, PrecModel** out) {
       }
     e = upload(pm, tab, &pm->head_table);
   }
+  if (products && e == hipSuccess) e = build_branch_table(m, pm, false);
   if (e == hipSuccess && hp.has_blend) {
     int di = hp.n_species;
     std::vector<int> dims = hp.blend_dims;
